@@ -226,10 +226,11 @@ int lbfast_get_scales(lbfast_t h, float out[10]);
 /* Launch shape: rows per tile (4, 6, 8 or 14 -- at most 8 with two sites
  * per lane or with LBF_D3Q27H; LBF_E_UNSUPPORTED if the tile's LDS would
  * exceed 160 KiB) and z-planes per workgroup (>= 1); 0 keeps
- * the current value.  The default z-planes per workgroup follow the grid: at
- * most ~512 workgroups (~1024 for F64 with two sites per lane) in chunks of
- * >= 64 planes, or, where that leaves fewer than 128 workgroups, enough
- * workgroups in chunks of >= 8 planes; a z_chunk set here replaces that rule.
+ * the current value.  Until rows or sites per lane are set, the library takes
+ * the shape of the least modelled time for the grid, storage and velocity set
+ * (from there on it starts from 8 rows, F64 6, or 4 with two sites per lane).
+ * The z-planes per workgroup follow the same model, down to one plane on
+ * small grids; a z_chunk set here replaces it.
  * Every shape computes the same formulas per site; the
  * tile heights are separately compiled, so results may differ between shapes
  * in the last bits (floating-point contraction), while one shape is bitwise
@@ -241,7 +242,9 @@ int lbfast_set_launch(lbfast_t h, int tile_rows, int z_chunk);
  * most 8 rows) or 3 (192-wide tiles, 3-wide accesses; F32 storage, LBF_D3Q19
  * or LBF_D3Q27, one component, nx divisible by 3, tiles of at most 8 rows;
  * enabling the two-component variant returns to one site per lane, as it
- * does from two with variable density or viscosity).  The default is 2 where
+ * does from two with variable density or viscosity).  The default
+ * follows the model (lbfast_set_launch); for 16-bit storage, and where rows
+ * are set without sites, it is 2 where
  * nx is even and at least 128 and the 128-wide tiles leave no more of the
  * last tile empty than 64-wide ones, else 3 where nx is divisible by 3 and
  * at least 192 and 192-wide tiles leave no more empty (F32, LBF_D3Q19 or
@@ -255,8 +258,9 @@ int lbfast_set_lane_sites(lbfast_t h, int sites);
 /* Order in which the workgroups of the marching kernels (step, checkpointed
  * forward pass, adjoint) are handed to the GPU's 8 XCDs (each with its own
  * L2), for the calls that follow: 0 = automatic (contiguous
- * tile ranges per XCD for F64 storage and for F32 with LBF_D3Q27 and
- * LBF_D3Q27H, the hardware's order otherwise, as measured at 512^3),
+ * tile ranges per XCD for states that fit the last-level cache but the
+ * smallest, and for F64 grids of more than 256 tile columns, the hardware's
+ * order otherwise),
  * 1 = the hardware's order (consecutive workgroups on the XCDs in turn),
  * 2 = a contiguous range of tiles per XCD.  A launch choice only: every
  * order computes bitwise the same results.  LBF_E_ARG for other values. */
@@ -338,7 +342,8 @@ int lbfast_forward_checkpointed(lbfast_t h, int64_t nsteps, int64_t every, void*
 /* Launch shape of the adjoint step: x-sites per lane (0 = automatic, 1, or 2
  * or 3 for F32 storage with nx divisible by it) and tile rows (0 = automatic,
  * 4, 6, 8 or 14; with two or three sites per lane 4 or 6, and 4 for
- * LBF_D3Q27).  Automatic: one site per lane, 8-row tiles (F64: 6).  Every
+ * LBF_D3Q27).  Automatic: one site per lane, 8-row tiles (F64: 6), lower ones
+ * on small grids.  Every
  * shape computes the same formulas; results may differ in the last bits. */
 int lbfast_set_adjoint_launch(lbfast_t h, int sites, int tile_rows);
 size_t lbfast_adjoint_work_bytes(lbfast_t h, int64_t every);

@@ -42,6 +42,7 @@ struct Adjoint {
   static constexpr int Q = Q_;
   static constexpr bool kThreeSites = std::is_same_v<C_, float>;
   static constexpr bool kStencil = false;
+  static constexpr bool kCachedForms = false;
   using C = C_;
   using T = C_;
   // lambda(t+1) and F of a site; destinations also read u(t+1), u(t) and
@@ -135,7 +136,7 @@ struct Adjoint {
     }
   }
 
-  template <int NS>
+  template <int CPOL, int NS>
   static __device__ __forceinline__ void finish(const StepArgs& a, const Sums<C> (&acc)[NS],
                                                 const Carry (&cc)[NS], int64_t pb, uint32_t off,
                                                 uint32_t plane_bytes) {
@@ -185,7 +186,7 @@ struct Adjoint {
 #pragma unroll
       for (int s = 0; s < NS; ++s) v[s] = out[s][k];
       C* base = k < 10 ? lam + (k * a.N + pb) : gf + ((k - 10) * a.N + pb);
-      buf_store_nt_n<C, NS>(v, plane_rsrc(base, plane_bytes), off);
+      buf_store_n<CPOL, C, NS>(v, plane_rsrc(base, plane_bytes), off);
     }
   }
 };

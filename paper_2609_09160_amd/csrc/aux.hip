@@ -244,7 +244,7 @@ __global__ void stream_probe_kernel(const float* __restrict__ src, float* __rest
     for (int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * kThreads) {
       const uint32_t off = static_cast<uint32_t>(i * sizeof(float));
-      buf_store_nt<float>(buf_load<float>(rs, off), rd, off);
+      buf_store_cpol<float>(buf_load<float>(rs, off), rd, off);
     }
   }
 }

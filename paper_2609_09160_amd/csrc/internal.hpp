@@ -33,6 +33,7 @@ struct StepArgs {
   int64_t N;           // plane stride = nx*ny*nz
   int tiles_x, tiles_y, zchunks, zchunk;
   int lane_sites;      // consecutive x-sites per lane: 1, 2 or 3 (tile width 64, 128, 192)
+  int cached;          // plain stores (march_cached below), else non-temporal
   int xcd_remap;       // give each XCD a contiguous range of tiles (else hardware order)
   double omega;
   double F[3];         // uniform force (used when Ffield == nullptr)
@@ -49,6 +50,13 @@ struct StepArgs {
   const void* state_new;  // moments at t+1
   void* gF;               // 3 planes, dJ/dF accumulated in place
 };
+
+// Forms of the step with plain stores exist for one x-site per lane and
+// tiles of 6 rows and more: the shapes of the grids whose states fit the
+// last-level cache and are large enough for it to matter.
+constexpr bool march_cached(int lane_sites, int tile_rows) {
+  return lane_sites == 1 && tile_rows >= 6;
+}
 
 // rows per tile supported by the step kernel
 constexpr int kTileRowsSupported[] = {4, 6, 8, 14};

@@ -143,9 +143,11 @@ struct lbfast_ctx {
   float scale[10];
   float inv_scale[10];
   bool scales_fixed = false;
-  int tile_rows = 8;
-  int z_chunk = 0;
+  int tile_rows = 8;       // launch shape once the caller has chosen rows or sites
   int lane_sites = 1;
+  bool shape_set = false;
+  int auto_sites = 1, auto_rows = 4;  // launch shape until then
+  int z_chunk = 0;
   bool two_phase = false;
   lbfast_phase_params pp;
   void* phi[2] = {nullptr, nullptr};  // phase field, two time levels
@@ -174,12 +176,188 @@ size_t lds_bytes(int Q, int storage, int tile_rows, int lane_sites, bool stencil
 }
 constexpr size_t kLdsLimit = 160 * 1024;
 
-// default launch shape (measured on MI355X at 512^3): two x-sites per lane
+// What decides the time of one march (a step or an adjoint step) besides its
+// launch shape.
+struct MarchForm {
+  int Q, storage;
+  bool stencil;          // one more LDS slot (two-component step)
+  double read, write;    // bytes per site
+  int streams;           // separate arrays read at an x-halo site
+  double l0, l1, busy;   // us per plane, see march_us
+};
+
+// Both state buffers within the 256 MB last-level cache, with room for the
+// rest: stores then leave the new state there (plain stores).  Measured where
+// it turns: FP32 144^3 (2 x 119 MB) 84 us with plain stores against 87 with
+// non-temporal ones, 160^3 (2 x 164 MB) 95 against 91.
+constexpr double kCacheStateBytes = 120e6;
+
+bool fits_cache(const lbfast_ctx* h) {
+  return static_cast<double>(lbfast_buffer_bytes(&h->p)) <= kCacheStateBytes;
+}
+
+// phases of unequal density or viscosity, or a density other than 1: the
+// step reads the phase field for a density and relaxation rate per site
+bool variable_properties(const lbfast_ctx* h) {
+  return h->pp.rho_l != 1.0 || h->pp.rho_h != 1.0 || h->pp.tau_l != h->pp.tau_h;
+}
+
+// 16-bit forms whose stored words depend on the launch shape: the two
+// copies of a plane in the march's unrolled loop (even and odd planes of a
+// chunk) and the tile heights contract FP32 differently there, and BF16's
+// stochastic rounding turns any difference into one of 2^-8.  They keep the
+// shape that the width gives and the chunks that go with it.
+bool shape_by_width(const lbfast_ctx* h) {
+  return is_16bit(h->p.storage) &&
+         (h->p.storage == LBF_BF16S || h->p.lattice == LBF_D3Q27H || h->two_phase);
+}
+
+// States of at least a few MB gain from what the cache keeps (plain stores,
+// contiguous tile ranges per XCD); smaller ones lose a little (64^3 FP32, 10.5
+// MB: 9.0 us non-temporal, 9.3 plain; 10.0 contiguous; FP16 32 x 136 x 224, 20
+// MB, 1.6% slower with both, 112^3, 28 MB, 5% faster).
+bool cache_matters(const lbfast_ctx* h) {
+  const double least = is_16bit(h->p.storage) ? 24e6 : 11e6;
+  return fits_cache(h) && static_cast<double>(lbfast_buffer_bytes(&h->p)) >= least;
+}
+
+// Whether a step in this shape stores plainly.  Not 16-bit storage with D3Q27h,
+// where the compiler contracts the two forms differently (see model_launch).
+bool step_cached(const lbfast_ctx* h, int S, int ty) {
+  return cache_matters(h) && !h->two_phase && lbf::march_cached(S, ty) &&
+         !(h->p.lattice == LBF_D3Q27H && is_16bit(h->p.storage));
+}
+
+MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
+  MarchForm f{};
+  f.Q = h->p.lattice;
+  f.storage = h->p.storage;
+  f.stencil = h->two_phase;
+  const double e = static_cast<double>(elem_bytes(f.storage));
+  const double c = f.storage == LBF_F64 ? 8.0 : 4.0;
+  f.read = f.write = static_cast<double>(state_planes(f.storage)) * e;
+  f.streams = f.storage == LBF_F16SU ? 4 : (is_16bit(f.storage) ? 3 : 10);
+  if (h->Ffield || h->two_phase) f.read += 3 * c, f.streams += 3;
+  if (h->two_phase) f.read += c, f.write += 3 * c, f.streams += 1;
+  if (adjoint) f.read = 22 * c, f.write = 13 * c, f.streams = 13, f.stencil = false;
+  // fitted to the times of 250 to 900 launch shapes on each of 67 grids (8 x
+  // 29 x 168 to 512^3), per velocity set and compute type; the 27h FP64 one
+  // is scaled from its FP32 one
+  const bool f64 = f.storage == LBF_F64;
+  if (f.Q == LBF_D3Q19) {
+    f.l0 = 0.45, f.l1 = f64 ? 0.15 : 0.07, f.busy = f64 ? 0.19 : 0.09;
+  } else if (f.Q == LBF_D3Q27) {
+    f.l0 = f64 ? 0.8 : 0.6, f.l1 = f64 ? 0.185 : 0.1, f.busy = f64 ? 0.3 : 0.135;
+  } else {
+    f.l0 = f64 ? 1.5 : 1.15, f.l1 = f64 ? 0.1 : 0.045, f.busy = f64 ? 0.4 : 0.175;
+  }
+  // the stencils of the two-component step, and the adjoint's 22 values per
+  // site, by the same measure
+  const double heavier = h->two_phase ? 1.25 : (adjoint ? 1.5 : 1.0);
+  f.l0 *= heavier, f.l1 *= heavier, f.busy *= heavier;
+  return f;
+}
+
+// Modelled time in us of a march with S sites per lane, ty tile rows and
+// z-chunks of zc planes (up to a constant).  A workgroup runs zc + 2 planes (an
+// even number); alone on a CU a plane takes l0 + l1 S (ty + 1) (latency and
+// barriers), and n workgroups on one CU at least n busy S (ty + 1) (issue), so
+// that what counts is the number of workgroups on the fullest of the 256 CUs:
+// grids run best in one wave of at most 256.  Against that stands the memory:
+// the planes and their y and z halos, 128 bytes for every x-halo site and
+// stream, read at 9 TB/s, and the stores at 5.6 TB/s (plain ones, which stay
+// in the cache, are not counted); more than one workgroup per CU drift apart
+// and lose halo lines.  The shape it picks takes 1.03 times as long as the best
+// one of the sweep in the geometric mean (the rule before it, 64-plane chunks
+// and the tile height by storage form alone, 1.6 times).
+double march_us(const MarchForm& f, int64_t nx, int64_t ny, int64_t nz, bool fits, bool cached,
+                int S, int ty, int64_t zc) {
+  const double tx = static_cast<double>(ceil_div(nx, 64 * S));
+  const double tyn = static_cast<double>(ceil_div(ny, ty));
+  const double nch = static_cast<double>(ceil_div(nz, zc));
+  const double N = static_cast<double>(nx) * static_cast<double>(ny) * static_cast<double>(nz);
+  const double w = tx * tyn * nch;
+  const double planes = 2.0 * static_cast<double>(ceil_div(zc + 2, 2));
+  const double per_cu = std::ceil(w / 256.0);
+  const double fit_lds =
+      static_cast<double>(kLdsLimit / lds_bytes(f.Q, f.storage, ty, S, f.stencil));
+  const double resident = std::min(per_cu, std::max(1.0, std::min(fit_lds, 32.0 / (ty + 2))));
+  const double work = S * (ty + 1);
+  const double full = std::floor(per_cu / resident), rest = per_cu - full * resident;
+  const double lat = f.l0 + f.l1 * work, busy = f.busy * work;
+  const double issue = planes * (full * std::max(lat, resident * busy) +
+                                 (rest > 0 ? std::max(lat, rest * busy) : 0.0));
+  double read = f.read * N * (1.0 + 2.0 * 1.5 * tyn / static_cast<double>(ny) +
+                              2.0 * 2.0 * nch / static_cast<double>(nz)) +
+                1.6 * 2.0 * 128.0 * f.streams * tx * static_cast<double>(ny) *
+                    static_cast<double>(nz);
+  if (!fits && w > 256.0 && tx * tyn <= 256.0) read *= 1.1;
+  const double mem = (read / 9.0 + (cached ? 0.0 : f.write * N / 5.6)) * 1e-6;
+  return std::sqrt(issue * issue + mem * mem);
+}
+
+// The chunks of shape_by_width: at most ~512 workgroups in chunks of >= 64
+// planes, or enough workgroups in chunks of >= 8 planes.
+int64_t width_zchunk(const lbfast_ctx* h, int64_t cols) {
+  const int64_t by_blocks = std::max<int64_t>(1, 512 / cols);
+  const int64_t long_chunks = std::max<int64_t>(1, h->p.nz / 64);
+  if (cols * long_chunks >= 128) return ceil_div(h->p.nz, std::min(by_blocks, long_chunks));
+  return ceil_div(h->p.nz, std::min(ceil_div(512, cols), std::max<int64_t>(1, h->p.nz / 8)));
+}
+
+// z-planes per workgroup of a shape, and the modelled time with them
+int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, double* us) {
+  const int64_t nx = h->p.nx, ny = h->p.ny, nz = h->p.nz;
+  const int64_t cols = ceil_div(nx, 64 * S) * ceil_div(ny, ty);
+  const bool fits = fits_cache(h);
+  const bool cached = step_cached(h, S, ty);
+  int64_t best = nz;
+  double t_best = 0.0;
+  bool have = false;
+  auto consider = [&](int64_t zc) {
+    const double t = march_us(f, nx, ny, nz, fits, cached, S, ty, zc);
+    if (!have || t < t_best) t_best = t, best = zc, have = true;
+  };
+  if (!fits && cols >= 256) {
+    // a column for every CU: about 512 workgroups in chunks of >= 64 planes
+    // (512^3 FP32: 2.00 ms, one chunk per column 2.02), FP64 1024 (3.91 ms,
+    // one chunk per column 4.35)
+    const int64_t target = f.storage == LBF_F64 ? 1024 : 512;
+    consider(ceil_div(nz, std::min(std::max<int64_t>(1, target / cols),
+                                   std::max<int64_t>(1, nz / 64))));
+  } else {
+    // every distinct chunk length, up to some 8 workgroups per CU
+    int64_t last = 0;
+    for (int64_t k = 1; k <= nz; ++k) {
+      const int64_t zc = ceil_div(nz, k);
+      if (zc == last) {
+        k = ceil_div(nz, zc - 1) - 1;  // on to the next shorter chunk
+        continue;
+      }
+      last = zc;
+      if (k > 1 && cols * k > 2048) break;
+      consider(zc);
+      if (zc == 1) break;
+    }
+  }
+  if (us) *us = t_best;
+  return best;
+}
+
+// tile shapes built for the handle's step
+bool shape_built(const lbfast_ctx* h, int S, int ty) {
+  if (S == 2 && h->p.nx % 2 != 0) return false;
+  if (S == 3 && (h->p.nx % 3 != 0 || h->p.storage != LBF_F32 || h->p.lattice == LBF_D3Q27H ||
+                 h->two_phase))
+    return false;
+  if (ty > 8 && (S > 1 || h->p.lattice == LBF_D3Q27H || h->two_phase)) return false;
+  return lds_bytes(h->p.lattice, h->p.storage, ty, S, h->two_phase) <= kLdsLimit;
+}
+
+// The shape that explicit launch settings start from: two x-sites per lane
 // where nx allows it (even, at least one 128-wide tile), 8-row tiles (FP64:
-// 4 rows with two sites per lane, 6 with one) or the tallest that fits the
-// LDS; z-chunks only when the column tiles alone give too few workgroups.
-// D3Q27h in FP64 keeps one site per lane: two spill registers there.
-void default_launch(lbfast_ctx* h) {
+// 4 rows with two sites per lane, 6 with one) or the tallest that fits the LDS.
+void width_launch(lbfast_ctx* h) {
   // two sites per lane unless 128-wide tiles would leave more of the last
   // tile empty than 64-wide ones; else three (FP32, second-order sets) where
   // 192-wide tiles leave no more empty than 64-wide ones (measured at 192^3:
@@ -211,37 +389,106 @@ void default_launch(lbfast_ctx* h) {
   h->z_chunk = 0;
 }
 
-int resolve_zchunk(const lbfast_ctx* h, int lane_sites, int tile_rows, int* tiles_x, int* tiles_y,
-                   int* zchunks, int* zchunk) {
+// Default launch shape: the one of the least modelled time among those built,
+// but
+//   * 16-bit storage keeps the sites per lane that the width alone gives:
+//     the one- and two-site kernels contract FP32 differently, which shows in 2%
+//     of the stored 16-bit words after ten steps, and a run's values should not
+//     depend on the other extents.  Tile heights and chunk lengths agree bit for
+//     bit for FP16 with D3Q19 and D3Q27; elsewhere they are kept too
+//     (shape_by_width);
+//   * FP64: one site per lane for D3Q27 and D3Q27h (two spill or leave one
+//     short workgroup per CU), and for D3Q19 beyond the cache two sites where
+//     the width suits them, with 4 rows (256^3: 497 us, 6 rows 575, one site
+//     and 14 rows 637);
+//   * variable density or viscosity: one site per lane (two spill; 256^3 FP32
+//     0.80 ms against 0.57);
+//   * 6 rows at most with three sites (8 spill with a force field: 192^3 143 us
+//     against 199), and, for the two-component step with D3Q27 and D3Q27h, with
+//     two sites or FP64 (256^3 FP32 645 us with two sites and 8 rows, 542 with
+//     one; 192^3 FP64 938 us with 8 rows, 654 with 6).
+void model_launch(lbfast_ctx* h) {
+  const int64_t nx = h->p.nx;
+  const bool f64 = h->p.storage == LBF_F64;
+  const bool two = nx % 2 == 0 && nx >= 128 &&
+                   ceil_div(nx, 128) * 128 - nx <= ceil_div(nx, 64) * 64 - nx;
+  const bool one_only = (h->two_phase && variable_properties(h)) ||
+                        (f64 && h->p.lattice != LBF_D3Q19);
+  if (shape_by_width(h)) {
+    h->auto_sites = h->lane_sites;
+    h->auto_rows = h->tile_rows;
+    return;
+  }
+  const MarchForm f = march_form(h);
+  double t_best = 0.0;
+  bool have = false;
+  for (int S = 1; S <= 3; ++S) {
+    if (one_only && S != 1) continue;
+    if (is_16bit(h->p.storage) && !one_only && S != (two ? 2 : 1)) continue;
+    for (int ty : lbf::kTileRowsSupported) {
+      if (!shape_built(h, S, ty)) continue;
+      if (ty > 6 && (S == 3 || (h->two_phase && h->p.lattice != LBF_D3Q19 && (S == 2 || f64))))
+        continue;
+      if (f64 && !one_only && !fits_cache(h) && (two ? (S != 2 || ty != 4) : S != 1)) continue;
+      double t;
+      (void)best_zchunk(h, f, S, ty, &t);
+      if (!have || t < t_best) {
+        have = true;
+        t_best = t;
+        h->auto_sites = S;
+        h->auto_rows = ty;
+      }
+    }
+  }
+}
+
+int step_sites(const lbfast_ctx* h) { return h->shape_set ? h->lane_sites : h->auto_sites; }
+int step_rows(const lbfast_ctx* h) { return h->shape_set ? h->tile_rows : h->auto_rows; }
+
+int resolve_zchunk(const lbfast_ctx* h, const MarchForm& f, int lane_sites, int tile_rows,
+                   int* tiles_x, int* tiles_y, int* zchunks, int* zchunk) {
   *tiles_x = static_cast<int>(ceil_div(h->p.nx, 64 * lane_sites));
   *tiles_y = static_cast<int>(ceil_div(h->p.ny, tile_rows));
   const int64_t cols = static_cast<int64_t>(*tiles_x) * *tiles_y;
   int64_t zc = h->z_chunk;
-  if (zc <= 0) {
-    // at most ~512 workgroups (~1024 for FP64 with two sites per lane, whose
-    // 4-row tiles are short) in chunks of >= 64 planes; measured on MI355X,
-    // shorter chunks or more workgroups cost 10-20% (256^3: 4 chunks of 64
-    // planes 61 GLUPS, 8 of 32 planes 52; 512^3: 2 chunks 65, 4 chunks 52).
-    // Grids too small for that many long chunks take enough workgroups
-    // first, in chunks of >= 8 planes.
-    const int64_t target = (h->p.storage == LBF_F64 && lane_sites == 2) ? 1024 : 512;
-    const int64_t by_blocks = std::max<int64_t>(1, target / cols);
-    const int64_t long_chunks = std::max<int64_t>(1, h->p.nz / 64);
-    int64_t nchunks;
-    if (cols * long_chunks >= 128) {
-      nchunks = std::min(by_blocks, long_chunks);
-    } else {
-      const int64_t want = ceil_div(target, cols);
-      const int64_t maxc = h->p.nz >= 8 ? h->p.nz / 8 : 1;
-      nchunks = want < 1 ? 1 : (want > maxc ? maxc : want);
-    }
-    zc = ceil_div(h->p.nz, nchunks);
-  }
+  if (zc <= 0)
+    zc = shape_by_width(h) ? width_zchunk(h, cols)
+                           : best_zchunk(h, f, lane_sites, tile_rows, nullptr);
   if (zc > h->p.nz) zc = h->p.nz;
   *zchunk = static_cast<int>(zc);
   *zchunks = static_cast<int>(ceil_div(h->p.nz, zc));
   if (static_cast<int64_t>(*zchunks) * cols > 0x7fffffff) return fail(LBF_E_ARG, "grid too large");
   return LBF_OK;
+}
+
+// Rows per tile of the adjoint step: 8 (FP64: 6, taller tiles spill), or fewer
+// where the states fit the cache and the model says so (FP32 16^3 to 48^3
+// 4 or 6 rows 11.5 to 12.5 us per step against 12.8 to 15.2).
+int adjoint_rows(const lbfast_ctx* h, const MarchForm& f, int sites) {
+  if (h->adj_rows) return h->adj_rows;
+  const int most = h->p.storage == LBF_F64 ? 6 : 8;
+  if (sites != 1 || !fits_cache(h)) return most;
+  int best = most;
+  double t_best = 0.0;
+  for (int ty : {most, 6, 4}) {
+    double t;
+    (void)best_zchunk(h, f, sites, ty, &t);
+    if (ty == most || t < t_best) t_best = t, best = ty;
+  }
+  return best;
+}
+
+// Block order: a contiguous range of tiles per XCD where the state is in the
+// cache and large enough for its halo lines to matter (201 x 97 x 113 FP32
+// 38 us against 47 in the hardware's order; 64^3 10.0 against 9.0), and for
+// FP64 with more columns than CUs (512^3 D3Q19 3.91 ms against 5.55).
+// Elsewhere the hardware's order: marches of one wave of workgroups keep
+// step by themselves, and several waves lose about 10% in the other.
+bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y) {
+  if (h->block_order != 0) return h->block_order == 2;
+  if (h->two_phase) return false;
+  if (fits_cache(h)) return cache_matters(h);
+  return h->p.storage == LBF_F64 && static_cast<int64_t>(tiles_x) * tiles_y > 256;
 }
 
 int check_handle(lbfast_t h) {
@@ -277,10 +524,12 @@ int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
   a->ny = static_cast<int>(h->p.ny);
   a->nz = static_cast<int>(h->p.nz);
   a->N = h->N;
-  a->lane_sites = h->lane_sites;
-  if (int rc = resolve_zchunk(h, h->lane_sites, h->tile_rows, &a->tiles_x, &a->tiles_y,
-                              &a->zchunks, &a->zchunk))
+  a->lane_sites = step_sites(h);
+  if (int rc = resolve_zchunk(h, march_form(h), a->lane_sites, step_rows(h), &a->tiles_x,
+                              &a->tiles_y, &a->zchunks, &a->zchunk))
     return rc;
+  a->cached = step_cached(h, a->lane_sites, step_rows(h));
+  a->xcd_remap = contiguous_order(h, a->tiles_x, a->tiles_y);
   a->omega = 1.0 / h->p.tau;
   for (int k = 0; k < 3; ++k) a->F[k] = h->Ffield ? 0.0 : h->p.force[k];
   for (int k = 0; k < 10; ++k) {
@@ -297,14 +546,6 @@ int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
     }
   }
   a->Ffield = h->Ffield;
-  // Block order, measured at 512^3 on one box with the two orders built as
-  // separate libraries and run interleaved: contiguous tile ranges per XCD
-  // are faster for FP64 (21% for D3Q19, 6% for D3Q27h) and for FP32 D3Q27
-  // (3%), the hardware order for 16-bit storage (2-5%); D3Q19 FP32 and its
-  // adjoint are equal within 1% and keep the hardware order.
-  a->xcd_remap = h->block_order == 2 ||
-                 (h->block_order == 0 &&
-                  (h->p.storage == LBF_F64 || (h->p.storage == LBF_F32 && h->p.lattice != LBF_D3Q19)));
   a->stochastic = h->p.rounding == LBF_ROUND_STOCHASTIC ||
                   (h->p.rounding == LBF_ROUND_AUTO && h->p.storage == LBF_BF16S);
   if (h->two_phase) {
@@ -329,7 +570,7 @@ uint32_t step_seed(uint64_t t) {
 }
 
 int launch_forward(const lbfast_ctx* h, const lbf::StepArgs& a) {
-  hipError_t e = lbf::launch_step(h->p.lattice, h->p.storage, h->tile_rows,
+  hipError_t e = lbf::launch_step(h->p.lattice, h->p.storage, step_rows(h),
                                   h->p.bc[1] == LBF_WALLS, a, h->stream);
   if (e != hipSuccess) return hip_fail(e, "step launch");
   return LBF_OK;
@@ -362,12 +603,6 @@ lbf::PhaseArgs phase_args(const lbfast_ctx* h) {
   a.nu_l = (h->pp.tau_l - 0.5) / 3.0;
   a.nu_h = (h->pp.tau_h - 0.5) / 3.0;
   return a;
-}
-
-// phases of unequal density or viscosity, or a density other than 1: the
-// step reads the phase field for a density and relaxation rate per site
-bool variable_properties(const lbfast_ctx* h) {
-  return h->pp.rho_l != 1.0 || h->pp.rho_h != 1.0 || h->pp.tau_l != h->pp.tau_h;
 }
 
 int check_adjoint_args(const lbfast_ctx* h, int64_t nsteps, int64_t every) {
@@ -483,7 +718,8 @@ int lbfast_create(const lbfast_params* p, void* stream, void* buf0, void* buf1, 
     for (int k = 0; k < 10; ++k) all = all && p->scale[k] != 0.0f;
     h->scales_fixed = all;
   }
-  default_launch(h);
+  width_launch(h);
+  model_launch(h);
 
   if (buf0) {
     h->buf[0] = buf0;
@@ -677,7 +913,9 @@ int lbfast_set_force_field(lbfast_t h, const void* F_dev, int dtype) {
   if (h->two_phase)
     return fail(LBF_E_STATE, "the two-component variant computes its own force field");
   if (!F_dev) {
+    const bool had = h->Ffield != nullptr;
     h->Ffield = nullptr;
+    if (had) model_launch(h);
     return LBF_OK;
   }
   const int want = (h->p.storage == LBF_F64) ? LBF_F64 : LBF_F32;
@@ -687,7 +925,9 @@ int lbfast_set_force_field(lbfast_t h, const void* F_dev, int dtype) {
   if (reinterpret_cast<uintptr_t>(F_dev) & (dtype == LBF_F64 ? 7 : 3))
     return fail(LBF_E_ARG, "force field is misaligned");
   if (!is_device_ptr(F_dev)) return fail(LBF_E_ARG, "force field must be device memory");
+  const bool had = h->Ffield != nullptr;
   h->Ffield = F_dev;
+  if (!had) model_launch(h);
   return LBF_OK;
 }
 
@@ -708,7 +948,10 @@ int lbfast_set_launch(lbfast_t h, int tile_rows, int z_chunk) {
                   tile_rows, lb);
   }
   if (z_chunk < 0) return fail(LBF_E_ARG, "z_chunk must be >= 0");
-  if (tile_rows) h->tile_rows = tile_rows;
+  if (tile_rows) {
+    h->tile_rows = tile_rows;
+    h->shape_set = true;
+  }
   if (z_chunk) h->z_chunk = z_chunk;
   return LBF_OK;
 }
@@ -746,6 +989,7 @@ int lbfast_set_lane_sites(lbfast_t h, int sites) {
   }
   h->lane_sites = sites;
   h->tile_rows = ty;
+  h->shape_set = true;
   return LBF_OK;
 }
 
@@ -851,7 +1095,8 @@ int lbfast_enable_two_phase(lbfast_t h, const lbfast_phase_params* pp) {
   h->pp = *pp;
   h->two_phase = true;
   h->pcur = 0;
-  // The two-component step has one- and two-site forms of at most 8 rows,
+  // A shape chosen by the caller is kept where it can be.  The two-component
+  // step has one- and two-site forms of at most 8 rows,
   // with one more LDS slot (phi(t+1)) than the one-component step.  With
   // variable density or viscosity, one site per lane: the two-site form
   // spills registers there (measured at 256^3 FP32: 0.80 ms against 0.57).
@@ -868,6 +1113,7 @@ int lbfast_enable_two_phase(lbfast_t h, const lbfast_phase_params* pp) {
         break;
       }
   }
+  model_launch(h);
   // F(0) of phi = 0: the body force alone
   lbf::PhaseArgs pa = phase_args(h);
   pa.phi_out = h->phi[0];
@@ -1032,9 +1278,10 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   // site per lane and 8-row tiles (FP64: 6); lbfast_set_adjoint_launch may
   // choose two or three sites per lane with 4- or 6-row tiles (FP32)
   aa.lane_sites = h->adj_sites ? h->adj_sites : 1;
-  const int adj_rows = h->adj_rows ? h->adj_rows : ((h->p.storage == LBF_F64) ? 6 : 8);
-  if (int rc = resolve_zchunk(h, aa.lane_sites, adj_rows, &aa.tiles_x, &aa.tiles_y, &aa.zchunks,
-                              &aa.zchunk))
+  const MarchForm adj_form = march_form(h, true);
+  const int adj_rows = adjoint_rows(h, adj_form, aa.lane_sites);
+  if (int rc = resolve_zchunk(h, adj_form, aa.lane_sites, adj_rows, &aa.tiles_x, &aa.tiles_y,
+                              &aa.zchunks, &aa.zchunk))
     return rc;
   const int64_t nseg = (nsteps + every - 1) / every;
   const bool walls_y = h->p.bc[1] == LBF_WALLS;

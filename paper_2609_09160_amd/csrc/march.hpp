@@ -21,14 +21,15 @@
 //   P::source<OWN, SEL>(a, raw, g[Q], carry)   g in units of 1/D (D =
 //                             Lat<Q>::D); halo sites (SEL != kSelAll) only
 //                             need the directions that enter the tile
-//   P::finish<S>(a, sums[S], carry[S], pb, off, plane_bytes)   store S
-//                             consecutive destinations
+//   P::finish<CPOL, S>(a, sums[S], carry[S], pb, off, plane_bytes)   store S
+//                             consecutive destinations (cache policy CPOL)
 //   P::kStencil               the destinations also need the gradient and
 //                             Laplacian of a scalar field (stencil.hpp):
 //                             every source site hands P::scalar(raw), the
 //                             skeleton stages it in LDS beside the values,
 //                             accumulates the stencils along z and passes
-//                             them to P::finish<S>(a, sums, carry, st[S], ...)
+//                             them to P::finish<CPOL, S>(a, sums, carry, st[S], ...)
+//   P::kCachedForms           there are forms with plain stores (march_cached)
 //
 // gfx950 mapping (own design; the paper's 8x8x8 shared-memory tiles are prior
 // art for another GPU):
@@ -142,7 +143,7 @@ __device__ __forceinline__ void accumulate(Sums<C>& S, C v) {
   if constexpr (cy * cz == -1) S.pyz -= v;
 }
 
-template <class P, int TY, bool WALLY, int S>
+template <class P, int TY, bool WALLY, int S, int CPOL>
 __global__ void __launch_bounds__(64 * (TY + 2)) march_kernel(const StepArgs a) {
   constexpr int Q = P::Q;
   using L = Lat<Q>;
@@ -306,9 +307,9 @@ __global__ void __launch_bounds__(64 * (TY + 2)) march_kernel(const StepArgs a) 
             for (int dx = 0; dx < 3; ++dx) n[dy][dx] = sgl[wv - 1 + dy][col + dx];
           so[s] = sr[s].plane(n);
         });
-        P::template finish<S>(a, acc, cd, so, pb, off, plane_bytes);
+        P::template finish<CPOL, S>(a, acc, cd, so, pb, off, plane_bytes);
       } else {
-        P::template finish<S>(a, acc, cd, pb, off, plane_bytes);
+        P::template finish<CPOL, S>(a, acc, cd, pb, off, plane_bytes);
       }
     }
     static_for<S>([&](auto SI) {
@@ -477,14 +478,14 @@ constexpr size_t march_lds_bytes() {
 }
 constexpr size_t kLdsLimit = 160 * 1024;
 
-template <class P, int TY, bool WALLY, int S>
+template <class P, int TY, bool WALLY, int S, int CPOL = kNonTemporal>
 hipError_t launch_march_s(const StepArgs& a, hipStream_t stream) {
   if constexpr (march_lds_bytes<P::Q, typename P::C, TY, S, P::kStencil>() > kLdsLimit) {
     return hipErrorInvalidConfiguration;
   } else {
     const int nb = a.tiles_x * a.tiles_y * a.zchunks;
-    hipLaunchKernelGGL((march_kernel<P, TY, WALLY, S>), dim3(nb), dim3(64 * (TY + 2)), 0, stream,
-                       a);
+    hipLaunchKernelGGL((march_kernel<P, TY, WALLY, S, CPOL>), dim3(nb), dim3(64 * (TY + 2)), 0,
+                       stream, a);
     return hipGetLastError();
   }
 }
@@ -504,6 +505,8 @@ hipError_t launch_march(const StepArgs& a, hipStream_t stream) {
     return hipErrorInvalidValue;
   }
   if (a.lane_sites != 1) return hipErrorInvalidValue;
+  if constexpr (P::kCachedForms && march_cached(1, TY))
+    if (a.cached) return launch_march_s<P, TY, WALLY, 1, kCached>(a, stream);
   return launch_march_s<P, TY, WALLY, 1>(a, stream);
 }
 

@@ -252,6 +252,9 @@ struct Forward {
   // second-order sets in FP32 storage
   static constexpr bool kThreeSites = ST == kF32 && !FNEXT && !FULL;
   static constexpr bool kStencil = FNEXT;  // grad and lap of phi(t+1)
+  // forms with plain stores, for states that fit the last-level cache (16-bit
+  // D3Q27h keeps the one form, whose words the other would not repeat)
+  static constexpr bool kCachedForms = !FNEXT && !(FULL && S::kNeq);
   // raw (still encoded) moments and force of one site, fetched a plane ahead;
   // with a time-dependent force also phi(t+1) (the stencil's scalar) and,
   // with variable properties, phi(t)
@@ -437,7 +440,7 @@ struct Forward {
 
   // two-component form: F(t+1) from the stencils, written out for the next
   // step, then the correction with it
-  template <int NS>
+  template <int CPOL, int NS>
   static __device__ __forceinline__ void finish(const StepArgs& a, const Sums<C> (&acc)[NS],
                                                 const Carry (&c)[NS],
                                                 const StencilOut<C> (&st)[NS], int64_t pb,
@@ -459,12 +462,12 @@ struct Forward {
     C* __restrict__ Fo = static_cast<C*>(a.Fout);
 #pragma unroll
     for (int k = 0; k < 3; ++k)
-      buf_store_nt_n<C, NS>(fo[k], plane_rsrc(Fo + (k * a.N + pb), plane_bytes * kFscale),
+      buf_store_n<CPOL, C, NS>(fo[k], plane_rsrc(Fo + (k * a.N + pb), plane_bytes * kFscale),
                             off * kFscale);
-    finish(a, acc, cf, pb, off, plane_bytes);
+    finish<CPOL>(a, acc, cf, pb, off, plane_bytes);
   }
 
-  template <int NS>
+  template <int CPOL, int NS>
   static __device__ __forceinline__ void finish(const StepArgs& a, const Sums<C> (&acc)[NS],
                                                 const Carry (&c)[NS], int64_t pb, uint32_t off,
                                                 uint32_t plane_bytes) {
@@ -538,7 +541,7 @@ struct Forward {
           const T4 h = {q[s][4 * j], q[s][4 * j + 1], q[s][4 * j + 2], q[s][4 * j + 3]};
           w[s] = __builtin_bit_cast(uint64_t, h);
         }
-        buf_store_nt_n<uint64_t, NS>(
+        buf_store_n<CPOL, uint64_t, NS>(
             w, plane_rsrc(reinterpret_cast<uint64_t*>(dst) + (j * a.N + pb), 4 * plane_bytes),
             4 * off);
       }
@@ -549,7 +552,7 @@ struct Forward {
           const T2 h = {q[s][kQ4], q[s][kQ4 + 1]};
           w[s] = __builtin_bit_cast(uint32_t, h);
         }
-        buf_store_nt_n<uint32_t, NS>(
+        buf_store_n<CPOL, uint32_t, NS>(
             w, plane_rsrc(reinterpret_cast<uint32_t*>(dst) + (kQ4 / 2 * a.N + pb), 2 * plane_bytes),
             2 * off);
       }
@@ -559,7 +562,7 @@ struct Forward {
       T v[NS];
 #pragma unroll
       for (int s = 0; s < NS; ++s) v[s] = q[s][k];
-      buf_store_nt_n<T, NS>(v, plane_rsrc(dst + (k * a.N + pb), plane_bytes), off);
+      buf_store_n<CPOL, T, NS>(v, plane_rsrc(dst + (k * a.N + pb), plane_bytes), off);
     }
   }
 };
