@@ -20,8 +20,6 @@
 // stepping, the fused step computes F(t+1) itself from phi(t+1).  Algorithmic
 // traffic at FP32: the phase update 20 B per lattice update (phi, u in; phi
 // out), the force march 16 B (phi in, F out).
-#include <atomic>
-
 #include "internal.hpp"
 #include "lattice.hpp"
 #include "stencil.hpp"
@@ -65,6 +63,7 @@ struct alignas(4 * sizeof(C)) Rec {
 // 16 rows: the record ring and the phi halo are a smaller share of the tile
 // than with 8 (measured 1% faster for the whole two-component step at 256^3)
 constexpr int kUpdRows = 16;
+constexpr int kLowRows = 4;
 // Loads ahead of use in the staged marches.  Iterations run in groups of
 // kGroup planes, with two register banks: at the start of a group the next
 // group's values are issued into one bank, and the current group is taken
@@ -89,17 +88,17 @@ constexpr int kGroup = 1;
 // A y wall's ghost slot computes the mirror site's record from the mirror
 // site's window and reverses v_y, so a ghost and its mirror hold the same
 // numbers and the flux through the wall cancels exactly.
-template <int ST>
-__global__ void __launch_bounds__(64 * kUpdRows) phase_kernel(
+template <int ST, int ROWS>
+__global__ void __launch_bounds__(64 * ROWS) phase_kernel(
     const typename Storage<ST>::C* __restrict__ phi, const typename Storage<ST>::T* __restrict__ st,
     typename Storage<ST>::C* __restrict__ out, int nx, int ny, int nz, int64_t N,
     typename Storage<ST>::C D, typename Storage<ST>::C lambda, typename Storage<ST>::C eps,
     float s1, float s2, float s3, int tiles_x, int tiles_y, int zchunk, bool walls_y) {
   using S = Storage<ST>;
   using C = typename S::C;
-  constexpr int PY = kUpdRows + 4, PX = 68;  // phi plane, two-site halo
-  constexpr int VY = kUpdRows + 2, VX = 66;  // record slots, one-site ring
-  constexpr int NT = 64 * kUpdRows;
+  constexpr int PY = ROWS + 4, PX = 68;  // phi plane, two-site halo
+  constexpr int VY = ROWS + 2, VX = 66;  // record slots, one-site ring
+  constexpr int NT = 64 * ROWS;
   constexpr int NP = PY * PX, NV = VY * VX;
   constexpr int PERP = (NP + NT - 1) / NT, PERV = (NV + NT - 1) / NT;
   constexpr int KZ = kPlaneK;
@@ -111,7 +110,7 @@ __global__ void __launch_bounds__(64 * kUpdRows) phase_kernel(
   b /= tiles_x;
   const int ty = b % tiles_y;
   const int zc = b / tiles_y;
-  const int x0 = tx * 64, y0 = ty * kUpdRows;
+  const int x0 = tx * 64, y0 = ty * ROWS;
   const int z0 = zc * zchunk, z1 = min(z0 + zchunk, nz);
   const int64_t plane = static_cast<int64_t>(nx) * ny;
   // Loads go through buffer resources of one plane with 32-bit in-plane byte
@@ -134,7 +133,7 @@ __global__ void __launch_bounds__(64 * kUpdRows) phase_kernel(
   }
   // record slots: the source site (the mirror site for a ghost), the top-left
   // of its 3 x 3 phi window in the staged plane, and whether v_y is reversed.
-  // Rows: the source row ys lies in [y0 - 1, y0 + kUpdRows], so the window
+  // Rows: the source row ys lies in [y0 - 1, y0 + ROWS], so the window
   // rows ys - y0 + 1 .. ys - y0 + 3 lie in [0, PY).
   uint32_t voff[PERV];
   int vwin[PERV];
@@ -479,53 +478,41 @@ __global__ void __launch_bounds__(64 * kUpdRows) grad_march_kernel(const C* __re
   }
 }
 
-// tiles and z-chunks of the staged passes: 64 x kUpdRows columns, z-chunks of
-// >= 8 planes, about as many workgroups as the device holds at once
-// (`target`), so that each CU runs as many marches as fit and they share
-// the memory latency
+// Tiles and z-chunks of the staged passes: 64 x `rows` columns and chunks of
+// zc planes, run as zc + `extra` iterations (an even number).  An iteration
+// takes `lat` us where a CU has one workgroup and at least `busy` us for each
+// workgroup on it, so the cost of a launch is the product with the workgroups
+// on the fullest of the 256 CUs; the chunk length of the least cost, down to
+// one plane on small grids.
 struct MarchGeom {
   int tiles_x, tiles_y, zchunk, blocks;
+  double cost;
 };
-MarchGeom march_geom(int nx, int ny, int nz, int target) {
-  MarchGeom m;
+MarchGeom march_geom(int nx, int ny, int nz, int rows, int extra, double lat, double busy) {
+  MarchGeom m{};
   m.tiles_x = (nx + 63) / 64;
-  m.tiles_y = (ny + kUpdRows - 1) / kUpdRows;
-  const int cols = m.tiles_x * m.tiles_y;
-  int nch = (target + cols - 1) / cols;
-  const int maxc = nz >= 8 ? nz / 8 : 1;
-  nch = nch < 1 ? 1 : (nch > maxc ? maxc : nch);
-  m.zchunk = (nz + nch - 1) / nch;
-  m.blocks = cols * ((nz + m.zchunk - 1) / m.zchunk);
+  m.tiles_y = (ny + rows - 1) / rows;
+  const int64_t cols = static_cast<int64_t>(m.tiles_x) * m.tiles_y;
+  int last = 0;
+  for (int k = 1; k <= nz; ++k) {
+    const int zc = (nz + k - 1) / k;
+    if (zc == last) {
+      k = (nz + zc - 2) / (zc - 1) - 1;  // on to the next shorter chunk
+      continue;
+    }
+    last = zc;
+    const int64_t blocks = cols * ((nz + zc - 1) / zc);
+    if (k > 1 && blocks > 4096) break;
+    const double per_cu = static_cast<double>((blocks + 255) / 256);
+    const double cost = (zc + extra + 1) / 2 * 2 * (per_cu * busy > lat ? per_cu * busy : lat);
+    if (k == 1 || cost < m.cost) {
+      m.cost = cost;
+      m.zchunk = zc;
+      m.blocks = static_cast<int>(blocks);
+    }
+    if (zc == 1) break;
+  }
   return m;
-}
-
-// workgroups of 64 x kUpdRows threads of kernel K resident on the current
-// device at once (compute units x blocks per unit); 512 if the runtime does
-// not say.  The answer depends only on the kernel and the device, so it is
-// asked once per device and kept.
-template <auto K>
-int resident_blocks() {
-  static std::atomic<int> cache[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return 512;
-  }
-  const bool slot = dev >= 0 && dev < 64;
-  if (slot) {
-    const int c = cache[dev].load(std::memory_order_relaxed);
-    if (c > 0) return c;
-  }
-  int cus = 0, per = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(K),
-                                                   64 * kUpdRows, 0) != hipSuccess ||
-      cus < 1 || per < 1) {
-    (void)hipGetLastError();
-    return 512;
-  }
-  if (slot) cache[dev].store(cus * per, std::memory_order_relaxed);
-  return cus * per;
 }
 
 int phase_grid(int64_t N) {
@@ -533,17 +520,34 @@ int phase_grid(int64_t N) {
   return static_cast<int>(b < 16384 ? (b < 1 ? 1 : b) : 16384);
 }
 
-template <int ST>
-hipError_t phase_step_st(const PhaseArgs& a, hipStream_t s) {
+template <int ST, int ROWS>
+hipError_t phase_step_rows(const PhaseArgs& a, const MarchGeom& m, hipStream_t s) {
   using C = typename Storage<ST>::C;
   using T = typename Storage<ST>::T;
-  const MarchGeom m = march_geom(a.nx, a.ny, a.nz, resident_blocks<phase_kernel<ST>>());
-  hipLaunchKernelGGL((phase_kernel<ST>), dim3(m.blocks), dim3(64 * kUpdRows), 0, s,
+  hipLaunchKernelGGL((phase_kernel<ST, ROWS>), dim3(m.blocks), dim3(64 * ROWS), 0, s,
                      static_cast<const C*>(a.phi), static_cast<const T*>(a.state),
                      static_cast<C*>(a.phi_out), a.nx, a.ny, a.nz, a.N, static_cast<C>(a.D),
                      static_cast<C>(a.lambda), static_cast<C>(a.eps), a.scale[1], a.scale[2],
                      a.scale[3], m.tiles_x, m.tiles_y, m.zchunk, a.walls_y != 0);
   return hipGetLastError();
+}
+
+// 16-row tiles for FP32 arithmetic on grids that fill the device with them, 4
+// rows on smaller ones (us per two-component step with the chunk of either that
+// is best there, 4 / 16 rows: 32^3 16 / 21, 64^3 23.6 / 24.9, 128^3 92.8 /
+// 91.7, 256^3 518 / 514), and always 4 rows in FP64, where 16 spill (128^3
+// 160 / 185).
+template <int ST>
+hipError_t phase_step_st(const PhaseArgs& a, hipStream_t s) {
+  if constexpr (ST == kF64) {
+    return phase_step_rows<ST, kLowRows>(
+        a, march_geom(a.nx, a.ny, a.nz, kLowRows, 5, 1.1, 0.9), s);
+  } else {
+    const MarchGeom tall = march_geom(a.nx, a.ny, a.nz, kUpdRows, 5, 2.0, 2.0);
+    const MarchGeom low = march_geom(a.nx, a.ny, a.nz, kLowRows, 5, 0.95, 0.55);
+    return low.cost < tall.cost ? phase_step_rows<ST, kLowRows>(a, low, s)
+                                : phase_step_rows<ST, kUpdRows>(a, tall, s);
+  }
 }
 
 }  // namespace
@@ -567,7 +571,7 @@ hipError_t force_st(const PhaseArgs& a, hipStream_t s) {
   const T* st = static_cast<const T*>(a.state);
   auto launch = [&](auto contrast) {
     using E = ForceEmit<ST, decltype(contrast)::value>;
-    const MarchGeom m = march_geom(a.nx, a.ny, a.nz, resident_blocks<grad_march_kernel<C, E>>());
+    const MarchGeom m = march_geom(a.nx, a.ny, a.nz, kUpdRows, 3, 1.0, 1.0);
     hipLaunchKernelGGL((grad_march_kernel<C, E>), dim3(m.blocks), dim3(64 * kUpdRows), 0, s, phi, a.nx, a.ny, a.nz,
                        m.tiles_x, m.tiles_y, m.zchunk, a.walls_y != 0,
                        E{st, static_cast<C*>(a.F), a.N, a});
