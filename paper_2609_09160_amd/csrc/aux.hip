@@ -89,6 +89,52 @@ __device__ __forceinline__ float stored_u(const U* u, int64_t i, float inv, floa
   }
 }
 
+// The stored words of V consecutive sites from site i on (V = 2: i and N
+// even), in the groups of plane_elem: 64-bit words of four planes, a 32-bit
+// word of a pair, a last plane on its own.
+template <class S, int V, typename F>
+__device__ __forceinline__ void each_site_word(int64_t i, int64_t N, F&& f) {
+  constexpr int q4 = S::kPlanes & ~3, q2 = q4 + (S::kPlanes & 2);
+  static_for<q4 / 4>([&](auto J) {
+    constexpr int k = 4 * decltype(J)::value;
+    f(std::integral_constant<int, k>{}, std::integral_constant<int, 4>{},
+      static_cast<int64_t>(k) * N + 4 * i);
+  });
+  if constexpr (q2 > q4)
+    f(std::integral_constant<int, q4>{}, std::integral_constant<int, 2>{},
+      static_cast<int64_t>(q4) * N + 2 * i);
+  if constexpr (S::kPlanes > q2)
+    f(std::integral_constant<int, q2>{}, std::integral_constant<int, 1>{},
+      static_cast<int64_t>(q2) * N + i);
+}
+template <class S, int V>
+__device__ __forceinline__ void load_site_words(const typename S::T* buf, int64_t i, int64_t N,
+                                                typename S::T (&q)[V][S::kPlanes]) {
+  each_site_word<S, V>(i, N, [&](auto K, auto W, int64_t at) {
+    constexpr int k = decltype(K)::value, w = decltype(W)::value;
+    using VT = typename S::T __attribute__((ext_vector_type(w * V)));
+    const VT x = *reinterpret_cast<const VT*>(buf + at);
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+      for (int j = 0; j < w; ++j) q[v][k + j] = x[v * w + j];
+  });
+}
+template <class S, int V>
+__device__ __forceinline__ void store_site_words(typename S::T* buf, int64_t i, int64_t N,
+                                                 const typename S::T (&q)[V][S::kPlanes]) {
+  each_site_word<S, V>(i, N, [&](auto K, auto W, int64_t at) {
+    constexpr int k = decltype(K)::value, w = decltype(W)::value;
+    using VT = typename S::T __attribute__((ext_vector_type(w * V)));
+    VT x;
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+      for (int j = 0; j < w; ++j) x[v * w + j] = q[v][k + j];
+    *reinterpret_cast<VT*>(buf + at) = x;
+  });
+}
+
 // user plane k (F64/F32) -> storage plane k; for deviation storage the planes
 // k >= 4 hold a2 - u u with u rounded as stored (u0..u2: the user's u planes)
 template <int ST, typename U>
@@ -143,6 +189,113 @@ __global__ void decode_kernel(const typename Storage<ST>::T* __restrict__ buf, U
     }
     user[i] = static_cast<U>(v);
   }
+}
+
+// Whole states between a user array in device memory and the storage: one
+// pass in place of one per plane.  Bound by memory.  With the planes of a
+// 16-bit state in 64-bit words, the plane-wise kernels above read each word once
+// for every plane in it, and the words of u again for each second-order plane
+// (512^3 FP16 and a float array: 7.8 ms in and 4.1 ms out for 8.1 GB; in one pass
+// 1.5 ms each, 5.4 TB/s; 32^3 60-70 us -> 16-21, launches).
+//
+// FP32 and FP64 states have the user array's own order, so that both
+// directions are one run of 10 N elements: a copy or a conversion with 16 bytes
+// per lane on the side that is written (512^3 FP32 2.20 ms -> 1.72, 6.2 TB/s;
+// FP32 to doubles with 32 bytes per lane lost a quarter to stores of half
+// lines).
+template <typename From, typename To, bool NT>
+__global__ void __launch_bounds__(kThreads) convert_flat_kernel(const From* __restrict__ src,
+                                                                To* __restrict__ dst, int64_t n) {
+  constexpr int V = 16 / sizeof(To);
+  using VF = From __attribute__((ext_vector_type(V), aligned(16)));
+  using VT = To __attribute__((ext_vector_type(V), aligned(16)));
+  const int64_t i = (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) * V;
+  if (i + V <= n) {
+    const VF v = *reinterpret_cast<const VF*>(src + i);
+    const VT w = __builtin_convertvector(v, VT);
+    if constexpr (NT)
+      __builtin_nontemporal_store(w, reinterpret_cast<VT*>(dst + i));
+    else
+      *reinterpret_cast<VT*>(dst + i) = w;
+  } else {
+    for (int64_t k = i; k < n; ++k) dst[k] = static_cast<To>(src[k]);
+  }
+}
+
+// 16-bit storage, V (1 or 2) consecutive sites per thread: 8 bytes per lane
+// and plane on the FP32 side with two.
+template <int ST, typename U, int V>
+__global__ void __launch_bounds__(kThreads) decode_all_kernel(
+    const typename Storage<ST>::T* __restrict__ buf, U* __restrict__ user, int64_t N, Scales s,
+    int nt) {
+  using S = Storage<ST>;
+  const int64_t i = (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) * V;
+  if (i >= N) return;
+  typename S::T q[V][S::kPlanes];
+  load_site_words<S, V>(buf, i, N, q);
+  using UV = U __attribute__((ext_vector_type(V)));
+  UV out[10];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    float u[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if constexpr (S::kSplitU)
+        u[c] = S::join(q[v][1 + c], q[v][10 + c], s.v[1 + c]);
+      else
+        u[c] = S::load(&q[v][1 + c], 0, s.v[1 + c]);
+    }
+#pragma unroll
+    for (int k = 0; k < 10; ++k) {
+      float x = (k >= 1 && k <= 3) ? u[k - 1] : S::load(&q[v][k], 0, s.v[k]);
+      if (k >= 4) x += u[a2_a(k)] * u[a2_b(k)];
+      out[k][v] = static_cast<U>(x);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 10; ++k) {
+    UV* p = reinterpret_cast<UV*>(user + k * N + i);
+    if (nt)
+      __builtin_nontemporal_store(out[k], p);
+    else
+      *p = out[k];
+  }
+}
+
+template <int ST, typename U, int V>
+__global__ void __launch_bounds__(kThreads) encode_all_kernel(
+    const U* __restrict__ user, typename Storage<ST>::T* __restrict__ buf, int64_t N, Scales inv,
+    Scales fwd) {
+  using S = Storage<ST>;
+  const int64_t i = (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) * V;
+  if (i >= N) return;
+  using UV = U __attribute__((ext_vector_type(V)));
+  UV m[10];
+#pragma unroll
+  for (int k = 0; k < 10; ++k) m[k] = *reinterpret_cast<const UV*>(user + k * N + i);
+  typename S::T q[V][S::kPlanes];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    float u[3];  // as stored
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const U x = m[1 + c][v];
+      u[c] = stored_u<ST>(&x, 0, inv.v[1 + c], fwd.v[1 + c]);
+    }
+#pragma unroll
+    for (int k = 0; k < 10; ++k) {
+      float x = static_cast<float>(m[k][v]);
+      if constexpr (S::kSplitU) {
+        if (k >= 1 && k <= 3) {
+          S::split_unit(x * inv.v[k], q[v][k], q[v][9 + k]);
+          continue;
+        }
+      }
+      if (k >= 4) x -= u[a2_a(k)] * u[a2_b(k)];
+      q[v][k] = S::encode(x, inv.v[k]);
+    }
+  }
+  store_site_words<S, V>(buf, i, N, q);
 }
 
 // max |value stored in plane k| over a user plane (deviation for k >= 4 when
@@ -375,6 +528,69 @@ hipError_t decode_st(int user_dtype, const void* buf, void* plane, int64_t N, in
   return hipGetLastError();
 }
 
+// Blocks of kThreads threads, `per` items each
+hipError_t one_shot_grid(int64_t n, int64_t per, dim3* grid) {
+  const int64_t b = (n + kThreads * per - 1) / (kThreads * per);
+  if (b > 0x7fffffff) return hipErrorInvalidValue;
+  *grid = dim3(static_cast<unsigned>(b));
+  return hipSuccess;
+}
+
+// Arrays of more than half the 256 MB last-level cache are written past it:
+// what is read next is no longer there anyway.
+constexpr int64_t kStreamBytes = 128 << 20;
+
+template <typename From, typename To>
+hipError_t convert_flat(const void* src, void* dst, int64_t n, hipStream_t st) {
+  constexpr int64_t V = 16 / sizeof(To);
+  dim3 grid;
+  if (hipError_t e = one_shot_grid(n, V, &grid); e != hipSuccess) return e;
+  const From* a = static_cast<const From*>(src);
+  To* b = static_cast<To*>(dst);
+  if (n * static_cast<int64_t>(sizeof(To)) > kStreamBytes)
+    hipLaunchKernelGGL((convert_flat_kernel<From, To, true>), grid, dim3(kThreads), 0, st, a, b, n);
+  else
+    hipLaunchKernelGGL((convert_flat_kernel<From, To, false>), grid, dim3(kThreads), 0, st, a, b, n);
+  return hipGetLastError();
+}
+
+template <int ST, typename U>
+hipError_t decode_all_16(const void* buf, void* user, int64_t N, const float* scale,
+                         hipStream_t st) {
+  using T = typename Storage<ST>::T;
+  const int64_t V = N % 2 ? 1 : 2;
+  const int nt = 10 * N * static_cast<int64_t>(sizeof(U)) > kStreamBytes;
+  dim3 grid;
+  if (hipError_t e = one_shot_grid(N, V, &grid); e != hipSuccess) return e;
+  const T* a = static_cast<const T*>(buf);
+  U* b = static_cast<U*>(user);
+  if (V == 2)
+    hipLaunchKernelGGL((decode_all_kernel<ST, U, 2>), grid, dim3(kThreads), 0, st, a, b, N,
+                       to_scales(scale), nt);
+  else
+    hipLaunchKernelGGL((decode_all_kernel<ST, U, 1>), grid, dim3(kThreads), 0, st, a, b, N,
+                       to_scales(scale), nt);
+  return hipGetLastError();
+}
+
+template <int ST, typename U>
+hipError_t encode_all_16(const void* user, void* buf, int64_t N, const float* inv,
+                         const float* fwd, hipStream_t st) {
+  using T = typename Storage<ST>::T;
+  const int64_t V = N % 2 ? 1 : 2;
+  dim3 grid;
+  if (hipError_t e = one_shot_grid(N, V, &grid); e != hipSuccess) return e;
+  const U* a = static_cast<const U*>(user);
+  T* b = static_cast<T*>(buf);
+  if (V == 2)
+    hipLaunchKernelGGL((encode_all_kernel<ST, U, 2>), grid, dim3(kThreads), 0, st, a, b, N,
+                       to_scales(inv), to_scales(fwd));
+  else
+    hipLaunchKernelGGL((encode_all_kernel<ST, U, 1>), grid, dim3(kThreads), 0, st, a, b, N,
+                       to_scales(inv), to_scales(fwd));
+  return hipGetLastError();
+}
+
 template <int ST>
 hipError_t maxabs_st(int user_dtype, const void* plane, const void* const u[3], int64_t N, int k,
                      const float* inv, const float* fwd, unsigned* out_bits, hipStream_t st) {
@@ -500,6 +716,52 @@ hipError_t launch_decode(int storage, int user_dtype, const void* buf, void* pla
     case kF16S: return decode_st<kF16S>(user_dtype, buf, plane, N, k, scale, s);
     case kBF16S: return decode_st<kBF16S>(user_dtype, buf, plane, N, k, scale, s);
     case kF16SU: return decode_st<kF16SU>(user_dtype, buf, plane, N, k, scale, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_encode_all(int storage, int user_dtype, const void* user, void* buf, int64_t N,
+                             const float* inv_scale, const float* scale, hipStream_t s) {
+  const bool u64 = user_dtype == kF64;
+  switch (storage) {
+    case kF64:
+      return u64 ? convert_flat<double, double>(user, buf, 10 * N, s)
+                 : convert_flat<float, double>(user, buf, 10 * N, s);
+    case kF32:
+      return u64 ? convert_flat<double, float>(user, buf, 10 * N, s)
+                 : convert_flat<float, float>(user, buf, 10 * N, s);
+    case kF16S:
+      return u64 ? encode_all_16<kF16S, double>(user, buf, N, inv_scale, scale, s)
+                 : encode_all_16<kF16S, float>(user, buf, N, inv_scale, scale, s);
+    case kBF16S:
+      return u64 ? encode_all_16<kBF16S, double>(user, buf, N, inv_scale, scale, s)
+                 : encode_all_16<kBF16S, float>(user, buf, N, inv_scale, scale, s);
+    case kF16SU:
+      return u64 ? encode_all_16<kF16SU, double>(user, buf, N, inv_scale, scale, s)
+                 : encode_all_16<kF16SU, float>(user, buf, N, inv_scale, scale, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_decode_all(int storage, int user_dtype, const void* buf, void* user, int64_t N,
+                             const float* scale, hipStream_t s) {
+  const bool u64 = user_dtype == kF64;
+  switch (storage) {
+    case kF64:
+      return u64 ? convert_flat<double, double>(buf, user, 10 * N, s)
+                 : convert_flat<double, float>(buf, user, 10 * N, s);
+    case kF32:
+      return u64 ? convert_flat<float, double>(buf, user, 10 * N, s)
+                 : convert_flat<float, float>(buf, user, 10 * N, s);
+    case kF16S:
+      return u64 ? decode_all_16<kF16S, double>(buf, user, N, scale, s)
+                 : decode_all_16<kF16S, float>(buf, user, N, scale, s);
+    case kBF16S:
+      return u64 ? decode_all_16<kBF16S, double>(buf, user, N, scale, s)
+                 : decode_all_16<kBF16S, float>(buf, user, N, scale, s);
+    case kF16SU:
+      return u64 ? decode_all_16<kF16SU, double>(buf, user, N, scale, s)
+                 : decode_all_16<kF16SU, float>(buf, user, N, scale, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -113,6 +113,12 @@ hipError_t launch_encode(int storage, int user_dtype, const void* plane, const v
                          hipStream_t stream);
 hipError_t launch_decode(int storage, int user_dtype, const void* buf, void* plane, int64_t N,
                          int k, const float* scale, hipStream_t stream);
+// The same for a whole state at once: user is a 10 x N array in device memory,
+// 16-byte aligned.
+hipError_t launch_encode_all(int storage, int user_dtype, const void* user, void* buf, int64_t N,
+                             const float* inv_scale, const float* scale, hipStream_t s);
+hipError_t launch_decode_all(int storage, int user_dtype, const void* buf, void* user, int64_t N,
+                             const float* scale, hipStream_t s);
 // max |stored value| of user plane k into out_bits[k] (float bits, zeroed before)
 hipError_t launch_maxabs(int storage, int user_dtype, const void* plane, const void* const u[3],
                          int64_t N, int k, const float* inv_scale, const float* scale,

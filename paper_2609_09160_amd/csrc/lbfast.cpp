@@ -857,7 +857,11 @@ int lbfast_set_moments(lbfast_t h, const void* m, int dtype, int on_device) {
     }
   }
   void* dst = h->buf[h->cur];
-  for (int k = 0; k < 10 && e == hipSuccess; ++k) {
+  // device arrays in one pass (the vector accesses want 16-byte alignment)
+  const bool whole = on_device && reinterpret_cast<uintptr_t>(m) % 16 == 0;
+  if (whole && e == hipSuccess)
+    e = lbf::launch_encode_all(h->p.storage, dtype, m, dst, N, h->inv_scale, h->scale, h->stream);
+  for (int k = 0; k < 10 && e == hipSuccess && !whole; ++k) {
     const void* src = plane(k, e);
     if (e == hipSuccess)
       e = lbf::launch_encode(h->p.storage, dtype, src, u, dst, N, k, h->inv_scale, h->scale,
@@ -893,7 +897,9 @@ int lbfast_get_moments(lbfast_t h, void* m, int dtype, int on_device) {
       return fail(LBF_E_NOMEM, "staging allocation failed");
     }
   }
-  for (int k = 0; k < 10 && e == hipSuccess; ++k) {
+  const bool whole = on_device && reinterpret_cast<uintptr_t>(m) % 16 == 0;
+  if (whole) e = lbf::launch_decode_all(h->p.storage, dtype, src, m, N, h->scale, h->stream);
+  for (int k = 0; k < 10 && e == hipSuccess && !whole; ++k) {
     void* dst = on_device ? static_cast<void*>(static_cast<char*>(m) + k * pbytes) : staging;
     e = lbf::launch_decode(h->p.storage, dtype, src, dst, N, k, h->scale, h->stream);
     if (e == hipSuccess && !on_device)
