@@ -202,14 +202,22 @@ bool variable_properties(const lbfast_ctx* h) {
   return h->pp.rho_l != 1.0 || h->pp.rho_h != 1.0 || h->pp.tau_l != h->pp.tau_h;
 }
 
-// 16-bit forms whose stored words depend on the launch shape: the two
-// copies of a plane in the march's unrolled loop (even and odd planes of a
-// chunk) and the tile heights contract FP32 differently there, and BF16's
-// stochastic rounding turns any difference into one of 2^-8.  They keep the
-// shape that the width gives and the chunks that go with it.
-bool shape_by_width(const lbfast_ctx* h) {
+// 16-bit forms whose stored words depend on the launch: the compiler contracts
+// FP32 differently in the two copies of a plane in the march's unrolled loop
+// (even and odd planes of a chunk) and, for some, between tile heights.  One
+// such difference moves a 16-bit word now and then, and BF16's stochastic
+// rounding makes every one a step of 2^-8.  FP16 with D3Q19 and D3Q27 is free of
+// both.  The others keep the parity of the planes that the chunks of
+// width_zchunk give, and where more than that matters these chunks themselves
+// and the rows of width_launch (BF16 D3Q19 48 x 104 x 46: 0.07% off after 29
+// steps in chunks of another even length).
+bool keeps_parity(const lbfast_ctx* h) {
   return is_16bit(h->p.storage) &&
-         (h->p.storage == LBF_BF16S || h->p.lattice == LBF_D3Q27H || h->two_phase);
+         (h->p.storage != LBF_F16S || h->p.lattice == LBF_D3Q27H || h->two_phase);
+}
+bool keeps_rows(const lbfast_ctx* h) {
+  return keeps_parity(h) &&
+         !(h->p.storage == LBF_F16SU && h->p.lattice != LBF_D3Q27H && !h->Ffield);
 }
 
 // States of at least a few MB gain from what the cache keeps (plain stores,
@@ -221,11 +229,12 @@ bool cache_matters(const lbfast_ctx* h) {
   return fits_cache(h) && static_cast<double>(lbfast_buffer_bytes(&h->p)) >= least;
 }
 
-// Whether a step in this shape stores plainly.  Not 16-bit storage with D3Q27h,
-// where the compiler contracts the two forms differently (see model_launch).
+// Whether a step in this shape stores plainly.  Not the 16-bit forms that keep
+// their rows, but for BF16 with D3Q19 and D3Q27: there the kernels with plain
+// stores are contracted differently, too.
 bool step_cached(const lbfast_ctx* h, int S, int ty) {
   return cache_matters(h) && !h->two_phase && lbf::march_cached(S, ty) &&
-         !(h->p.lattice == LBF_D3Q27H && is_16bit(h->p.storage));
+         (!keeps_rows(h) || (h->p.storage == LBF_BF16S && h->p.lattice != LBF_D3Q27H));
 }
 
 MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
@@ -296,9 +305,10 @@ double march_us(const MarchForm& f, int64_t nx, int64_t ny, int64_t nz, bool fit
   return std::sqrt(issue * issue + mem * mem);
 }
 
-// The chunks of shape_by_width: at most ~512 workgroups in chunks of >= 64
-// planes, or enough workgroups in chunks of >= 8 planes.
-int64_t width_zchunk(const lbfast_ctx* h, int64_t cols) {
+// Chunks of the shape of width_launch: at most ~512 workgroups in chunks of >=
+// 64 planes, or enough workgroups in chunks of >= 8 planes.
+int64_t width_zchunk(const lbfast_ctx* h) {
+  const int64_t cols = ceil_div(h->p.nx, 64 * h->lane_sites) * ceil_div(h->p.ny, h->tile_rows);
   const int64_t by_blocks = std::max<int64_t>(1, 512 / cols);
   const int64_t long_chunks = std::max<int64_t>(1, h->p.nz / 64);
   if (cols * long_chunks >= 128) return ceil_div(h->p.nz, std::min(by_blocks, long_chunks));
@@ -314,17 +324,30 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   int64_t best = nz;
   double t_best = 0.0;
   bool have = false;
+  // chunks of an even length (or one alone) leave every plane its parity; the
+  // forms that keep their rows also tell the first planes of a chunk apart
+  const int64_t by_width = keeps_parity(h) ? width_zchunk(h) : 0;
+  const bool even_only = by_width > 0;
+  const bool fixed = keeps_rows(h) || (even_only && by_width % 2 != 0 && by_width < nz);
+  // in contiguous order, chunks that come out whole on each of the 8 XCDs
+  // share all their halo lines there (201 x 97 x 113 D3Q27 FP32 with a field: 8
+  // chunks 53 us, 9 chunks 60)
+  const bool whole = !f.stencil && cache_matters(h) && h->block_order != 1;
   auto consider = [&](int64_t zc) {
-    const double t = march_us(f, nx, ny, nz, fits, cached, S, ty, zc);
+    double t = march_us(f, nx, ny, nz, fits, cached, S, ty, zc);
+    if (whole && ceil_div(nz, zc) % 8 == 0) t *= 0.95;
     if (!have || t < t_best) t_best = t, best = zc, have = true;
   };
-  if (!fits && cols >= 256) {
+  if (fixed) {
+    consider(by_width);
+  } else if (!fits && cols >= 256) {
     // a column for every CU: about 512 workgroups in chunks of >= 64 planes
     // (512^3 FP32: 2.00 ms, one chunk per column 2.02), FP64 1024 (3.91 ms,
     // one chunk per column 4.35)
     const int64_t target = f.storage == LBF_F64 ? 1024 : 512;
-    consider(ceil_div(nz, std::min(std::max<int64_t>(1, target / cols),
-                                   std::max<int64_t>(1, nz / 64))));
+    const int64_t zc = ceil_div(nz, std::min(std::max<int64_t>(1, target / cols),
+                                             std::max<int64_t>(1, nz / 64)));
+    consider(even_only && zc < nz ? zc + zc % 2 : zc);
   } else {
     // every distinct chunk length, up to some 8 workgroups per CU
     int64_t last = 0;
@@ -336,7 +359,7 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
       }
       last = zc;
       if (k > 1 && cols * k > 2048) break;
-      consider(zc);
+      if (!even_only || zc % 2 == 0 || zc == nz) consider(zc);
       if (zc == 1) break;
     }
   }
@@ -394,9 +417,7 @@ void width_launch(lbfast_ctx* h) {
 //   * 16-bit storage keeps the sites per lane that the width alone gives:
 //     the one- and two-site kernels contract FP32 differently, which shows in 2%
 //     of the stored 16-bit words after ten steps, and a run's values should not
-//     depend on the other extents.  Tile heights and chunk lengths agree bit for
-//     bit for FP16 with D3Q19 and D3Q27; elsewhere they are kept too
-//     (shape_by_width);
+//     depend on the other extents (see keeps_parity for what else it keeps);
 //   * FP64: one site per lane for D3Q27 and D3Q27h (two spill or leave one
 //     short workgroup per CU), and for D3Q19 beyond the cache two sites where
 //     the width suits them, with 4 rows (256^3: 497 us, 6 rows 575, one site
@@ -414,7 +435,7 @@ void model_launch(lbfast_ctx* h) {
                    ceil_div(nx, 128) * 128 - nx <= ceil_div(nx, 64) * 64 - nx;
   const bool one_only = (h->two_phase && variable_properties(h)) ||
                         (f64 && h->p.lattice != LBF_D3Q19);
-  if (shape_by_width(h)) {
+  if (keeps_rows(h)) {
     h->auto_sites = h->lane_sites;
     h->auto_rows = h->tile_rows;
     return;
@@ -451,9 +472,7 @@ int resolve_zchunk(const lbfast_ctx* h, const MarchForm& f, int lane_sites, int 
   *tiles_y = static_cast<int>(ceil_div(h->p.ny, tile_rows));
   const int64_t cols = static_cast<int64_t>(*tiles_x) * *tiles_y;
   int64_t zc = h->z_chunk;
-  if (zc <= 0)
-    zc = shape_by_width(h) ? width_zchunk(h, cols)
-                           : best_zchunk(h, f, lane_sites, tile_rows, nullptr);
+  if (zc <= 0) zc = best_zchunk(h, f, lane_sites, tile_rows, nullptr);
   if (zc > h->p.nz) zc = h->p.nz;
   *zchunk = static_cast<int>(zc);
   *zchunks = static_cast<int>(ceil_div(h->p.nz, zc));
@@ -486,7 +505,8 @@ int adjoint_rows(const lbfast_ctx* h, const MarchForm& f, int sites) {
 // step by themselves, and several waves lose about 10% in the other.
 bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y) {
   if (h->block_order != 0) return h->block_order == 2;
-  if (h->two_phase) return false;
+  // measured 6% slower for 16-bit D3Q27h at 267 x 122 x 127
+  if (h->two_phase || keeps_rows(h)) return false;
   if (fits_cache(h)) return cache_matters(h);
   return h->p.storage == LBF_F64 && static_cast<int64_t>(tiles_x) * tiles_y > 256;
 }
