@@ -1243,17 +1243,23 @@ int lbfast_forward_checkpointed(lbfast_t h, int64_t nsteps, int64_t every, void*
     h->cur ^= 1;
     return LBF_OK;
   }
+  if (nsteps == 0) return LBF_OK;
+  // The initial state is copied; a later checkpoint is written into its slot by
+  // the step that makes it, and read from there by the next one.
+  hipError_t e = hipMemcpyAsync(ck, h->buf[h->cur], bytes, hipMemcpyDeviceToDevice, h->stream);
+  if (e != hipSuccess) return hip_fail(e, "checkpoint copy");
+  int cur = h->cur;
+  const void* at = h->buf[cur];
   for (int64_t t = 0; t < nsteps; ++t) {
-    if (t % every == 0) {
-      hipError_t e = hipMemcpyAsync(ck + (t / every) * bytes, h->buf[h->cur], bytes,
-                                    hipMemcpyDeviceToDevice, h->stream);
-      if (e != hipSuccess) return hip_fail(e, "checkpoint copy");
-    }
-    a.src = h->buf[h->cur];
-    a.dst = h->buf[h->cur ^ 1];
+    a.src = at;
+    if ((t + 1) % every == 0 && t + 1 < nsteps)
+      a.dst = ck + (t + 1) / every * bytes;
+    else
+      a.dst = h->buf[cur ^= 1];
     if (int rc = launch_forward(h, a)) return rc;
-    h->cur ^= 1;
+    at = a.dst;
   }
+  h->cur = cur;
   return LBF_OK;
 }
 
@@ -1293,9 +1299,18 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   char* work = static_cast<char*>(work_dev);
   // work: recomputed states 1..every of a segment, then two adjoint buffers
   void* lam[2] = {work + every * bytes, work + (every + 1) * bytes};
-  e = hipMemcpyAsync(lam[0], lambda_T_dev, bytes, hipMemcpyDeviceToDevice, h->stream);
-  if (e != hipSuccess) return hip_fail(e, "adjoint copy");
-  int cur = 0;
+  // The first adjoint step reads lambda_T and the last one writes lambda0 where
+  // they lie, unless they are one array and there is one step.
+  const char* lT = static_cast<const char*>(lambda_T_dev);
+  const char* l0 = static_cast<const char*>(lambda0_dev);
+  const bool apart = !l0 || nsteps > 1 || lT + bytes <= l0 || l0 + bytes <= lT;
+  const void* lam_src = lambda_T_dev;
+  if (!apart || reinterpret_cast<uintptr_t>(lT) % 16 != 0) {
+    e = hipMemcpyAsync(lam[0], lambda_T_dev, bytes, hipMemcpyDeviceToDevice, h->stream);
+    if (e != hipSuccess) return hip_fail(e, "adjoint copy");
+    lam_src = lam[0];
+  }
+  const bool l0_direct = l0 && reinterpret_cast<uintptr_t>(l0) % 16 == 0;
   lbf::StepArgs fa, aa;
   if (int rc = step_args(h, &fa)) return rc;
   aa = fa;
@@ -1329,17 +1344,18 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
       if (int rc = launch_forward(h, fa)) return rc;
     }
     for (int64_t j = len - 1; j >= 0; --j) {  // sweep it backwards
-      aa.src = lam[cur];
-      aa.dst = lam[cur ^ 1];
+      aa.src = lam_src;
+      aa.dst = lam_src == lam[0] ? lam[1] : lam[0];
+      if (l0_direct && seg == 0 && j == 0) aa.dst = lambda0_dev;
       aa.state_old = state(j);
       aa.state_new = state(j + 1);
       e = lbf::launch_adjoint(h->p.lattice, h->p.storage, adj_rows, walls_y, aa, h->stream);
       if (e != hipSuccess) return hip_fail(e, "adjoint launch");
-      cur ^= 1;
+      lam_src = aa.dst;
     }
   }
-  if (lambda0_dev) {
-    e = hipMemcpyAsync(lambda0_dev, lam[cur], bytes, hipMemcpyDeviceToDevice, h->stream);
+  if (lambda0_dev && !l0_direct) {
+    e = hipMemcpyAsync(lambda0_dev, lam_src, bytes, hipMemcpyDeviceToDevice, h->stream);
     if (e != hipSuccess) return hip_fail(e, "adjoint copy");
   }
   return LBF_OK;
