@@ -43,6 +43,7 @@ struct Adjoint {
   static constexpr bool kThreeSites = std::is_same_v<C_, float>;
   static constexpr bool kStencil = false;
   static constexpr bool kCachedForms = false;
+  static constexpr bool kSlabForms = true;
   using C = C_;
   using T = C_;
   // lambda(t+1) and F of a site; destinations also read u(t+1), u(t) and
@@ -197,6 +198,18 @@ hipError_t launch_adjoint_type(int Q, int tile_rows, bool walls_y, bool ffield,
   // A destination reads 22 values: one site per lane fits 10-wave workgroups
   // (8-row tiles); two or three sites per lane (FP32) need the register room
   // of shorter tiles (4 or 6 rows: at most 2 waves per SIMD).
+  if (a.slab) {
+    const bool q19 = Q == 19;
+    if (!q19 && Q != 27) return hipErrorInvalidValue;
+    auto go = [&](auto QQ, auto FF) {
+      using P = Adjoint<decltype(QQ)::value, C, decltype(FF)::value>;
+      return walls_y ? launch_slab<P, true>(a, s) : launch_slab<P, false>(a, s);
+    };
+    using Q19 = std::integral_constant<int, 19>;
+    using Q27 = std::integral_constant<int, 27>;
+    if (ffield) return q19 ? go(Q19{}, std::true_type{}) : go(Q27{}, std::true_type{});
+    return q19 ? go(Q19{}, std::false_type{}) : go(Q27{}, std::false_type{});
+  }
 #define LBF_ADJ_CASE(QQ, TYY, SS)                                                     \
   if (Q == QQ && tile_rows == TYY && a.lane_sites == SS) {                            \
     if (walls_y)                                                                     \

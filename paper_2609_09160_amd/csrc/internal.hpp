@@ -33,6 +33,7 @@ struct StepArgs {
   int64_t N;           // plane stride = nx*ny*nz
   int tiles_x, tiles_y, zchunks, zchunk;
   int lane_sites;      // consecutive x-sites per lane: 1, 2 or 3 (tile width 64, 128, 192)
+  int slab;            // one plane per workgroup, no march (kSlabRows rows, zchunks = nz)
   int cached;          // plain stores (march_cached below), else non-temporal
   int xcd_remap;       // give each XCD a contiguous range of tiles (else hardware order)
   double omega;
@@ -57,6 +58,9 @@ struct StepArgs {
 constexpr bool march_cached(int lane_sites, int tile_rows) {
   return lane_sites == 1 && tile_rows >= 6;
 }
+
+// Tile rows of the one-plane form (one x-site per lane).
+constexpr int kSlabRows = 4;
 
 // rows per tile supported by the step kernel
 constexpr int kTileRowsSupported[] = {4, 6, 8, 14};

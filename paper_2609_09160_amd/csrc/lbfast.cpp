@@ -147,6 +147,7 @@ struct lbfast_ctx {
   int lane_sites = 1;
   bool shape_set = false;
   int auto_sites = 1, auto_rows = 4;  // launch shape until then
+  bool auto_slab = false;             // one plane per workgroup instead (no z_chunk set)
   int z_chunk = 0;
   bool two_phase = false;
   lbfast_phase_params pp;
@@ -367,6 +368,20 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   return best;
 }
 
+// Modelled time of the one-plane form, in march_us's terms: its workgroups take
+// 12.2 busy us each one after the other on a CU, and it has no chain of planes
+// before the first of them.
+double slab_us(const lbfast_ctx* h, const MarchForm& f) {
+  const double w = static_cast<double>(ceil_div(h->p.nx, 64) * ceil_div(h->p.ny, lbf::kSlabRows)) *
+                   static_cast<double>(h->p.nz);
+  return 12.2 * f.busy * std::ceil(w / 256.0) - 1.35;
+}
+
+// the one-plane form in place of a march that is modelled to take `march` us
+bool slab_pays(const lbfast_ctx* h, const MarchForm& f, double march) {
+  return fits_cache(h) && slab_us(h, f) < march;
+}
+
 // tile shapes built for the handle's step
 bool shape_built(const lbfast_ctx* h, int S, int ty) {
   if (S == 2 && h->p.nx % 2 != 0) return false;
@@ -435,6 +450,7 @@ void model_launch(lbfast_ctx* h) {
                    ceil_div(nx, 128) * 128 - nx <= ceil_div(nx, 64) * 64 - nx;
   const bool one_only = (h->two_phase && variable_properties(h)) ||
                         (f64 && h->p.lattice != LBF_D3Q19);
+  h->auto_slab = false;
   if (keeps_rows(h)) {
     h->auto_sites = h->lane_sites;
     h->auto_rows = h->tile_rows;
@@ -461,6 +477,27 @@ void model_launch(lbfast_ctx* h) {
       }
     }
   }
+  // not 16-bit storage: with a uniform force the one-plane form is contracted
+  // differently (FP16 D3Q19 33 x 70 x 40: some words off by one after 3 steps)
+  h->auto_slab = !is_16bit(h->p.storage) && slab_pays(h, f, t_best);
+}
+
+bool step_slab(const lbfast_ctx* h) { return !h->shape_set && h->z_chunk == 0 && h->auto_slab; }
+
+// launch geometry of the one-plane form
+void slab_args(const lbfast_ctx* h, lbf::StepArgs* a) {
+  a->slab = 1;
+  a->cached = 0;
+  a->lane_sites = 1;
+  a->tiles_x = static_cast<int>(ceil_div(h->p.nx, 64));
+  a->tiles_y = static_cast<int>(ceil_div(h->p.ny, lbf::kSlabRows));
+  a->zchunk = 1;
+  a->zchunks = static_cast<int>(h->p.nz);
+  // z-neighbours on one XCD once a CU has more than one workgroup (48^3 FP32
+  // 5.7 us, 7.7 in the hardware's order; 32^3 4.1 and 3.8)
+  a->xcd_remap = h->block_order != 0
+                     ? h->block_order == 2
+                     : static_cast<int64_t>(a->tiles_x) * a->tiles_y * h->p.nz > 256;
 }
 
 int step_sites(const lbfast_ctx* h) { return h->shape_set ? h->lane_sites : h->auto_sites; }
@@ -550,6 +587,7 @@ int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
     return rc;
   a->cached = step_cached(h, a->lane_sites, step_rows(h));
   a->xcd_remap = contiguous_order(h, a->tiles_x, a->tiles_y);
+  if (step_slab(h)) slab_args(h, a);
   a->omega = 1.0 / h->p.tau;
   for (int k = 0; k < 3; ++k) a->F[k] = h->Ffield ? 0.0 : h->p.force[k];
   for (int k = 0; k < 10; ++k) {
@@ -590,7 +628,8 @@ uint32_t step_seed(uint64_t t) {
 }
 
 int launch_forward(const lbfast_ctx* h, const lbf::StepArgs& a) {
-  hipError_t e = lbf::launch_step(h->p.lattice, h->p.storage, step_rows(h),
+  hipError_t e = lbf::launch_step(h->p.lattice, h->p.storage,
+                                  a.slab ? lbf::kSlabRows : step_rows(h),
                                   h->p.bc[1] == LBF_WALLS, a, h->stream);
   if (e != hipSuccess) return hip_fail(e, "step launch");
   return LBF_OK;
@@ -1321,9 +1360,16 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   aa.lane_sites = h->adj_sites ? h->adj_sites : 1;
   const MarchForm adj_form = march_form(h, true);
   const int adj_rows = adjoint_rows(h, adj_form, aa.lane_sites);
+  aa.slab = 0;
   if (int rc = resolve_zchunk(h, adj_form, aa.lane_sites, adj_rows, &aa.tiles_x, &aa.tiles_y,
                               &aa.zchunks, &aa.zchunk))
     return rc;
+  aa.xcd_remap = contiguous_order(h, aa.tiles_x, aa.tiles_y);
+  if (!h->adj_sites && !h->adj_rows && h->z_chunk == 0) {
+    double march;
+    (void)best_zchunk(h, adj_form, aa.lane_sites, adj_rows, &march);
+    if (slab_pays(h, adj_form, march)) slab_args(h, &aa);
+  }
   const int64_t nseg = (nsteps + every - 1) / every;
   const bool walls_y = h->p.bc[1] == LBF_WALLS;
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {

@@ -30,6 +30,7 @@
 //                             accumulates the stencils along z and passes
 //                             them to P::finish<CPOL, S>(a, sums, carry, st[S], ...)
 //   P::kCachedForms           there are forms with plain stores (march_cached)
+//   P::kSlabForms             ... and forms of slab_kernel
 //
 // gfx950 mapping (own design; the paper's 8x8x8 shared-memory tiles are prior
 // art for another GPU):
@@ -469,6 +470,197 @@ __global__ void __launch_bounds__(64 * (TY + 2)) march_kernel(const StepArgs a) 
   }
 }
 
+// One plane of destinations per workgroup, without a march: the form for grids
+// that leave a march only a few planes.  A workgroup owns a 64 x TY tile of one
+// plane and loads that plane and its two neighbours at once.  A value with c_z =
+// +1 arrives from the plane below, one with c_z = -1 from the plane above, so
+// every direction comes from one of the three planes and takes the LDS slot it
+// has in the march: one barrier, one wait for memory, 19 or 27 populations per
+// site in place of 3 x as many (the values of a neighbour plane that are not
+// used are never computed).  What a march of two planes takes is the chain of
+// its four planes, 0.96 us each for D3Q19 FP32, bound by the instructions of
+// one wave, and by neither the loads (three planes ahead instead of one: no
+// faster) nor the barriers (one a plane: no faster).  us per step, march / this:
+// 32^3 FP32 7.1 / 3.8, 64^3 9.9 / 7.1, 32^3 FP64 8.8 / 5.2; at 96^3, 19.4 / 23.5,
+// the two neighbour planes cost more than the chain.  They are read by three
+// workgroups, from L2 where the tiles of an XCD are contiguous in z
+// (a.xcd_remap).  Rows, columns, lanes and waves are those of march_kernel with
+// one site per lane.  8-row tiles took as long per row.
+template <class P, int TY, bool WALLY>
+__global__ void __launch_bounds__(64 * (TY + 2)) slab_kernel(const StepArgs a) {
+  constexpr int Q = P::Q;
+  using L = Lat<Q>;
+  using C = typename P::C;
+  using T = typename P::T;
+  using RawOwn = typename P::template Raw<true>;
+  using RawHalo = typename P::template Raw<false>;
+  using Carry = typename P::Carry;
+  constexpr int NP = L::NP, R = TY + 2, W = 66;
+  constexpr bool KS = P::kStencil;
+  __shared__ C lds[NP][R][W];
+  __shared__ C sgl[KS ? 3 : 1][KS ? R : 1][KS ? W : 1];  // the scalar of the three planes
+
+  const int lane = threadIdx.x & 63;
+  const int wv = threadIdx.x >> 6;
+  const int nx = a.nx, ny = a.ny, nz = a.nz;
+  const int64_t plane = static_cast<int64_t>(nx) * ny;
+  const int nb = static_cast<int>(gridDim.x), b0 = static_cast<int>(blockIdx.x);
+  int b = b0;
+  if (a.xcd_remap) {
+    const int q8 = nb >> 3, r8 = nb & 7, xcd = b0 & 7;
+    b = xcd * q8 + (xcd < r8 ? xcd : r8) + (b0 >> 3);
+  }
+  const int tyi = b % a.tiles_y;
+  b /= a.tiles_y;
+  const int txi = b % a.tiles_x;
+  const int z = b / a.tiles_x;
+  const int x0 = txi * 64, y0 = tyi * TY;
+  const uint32_t plane_bytes = static_cast<uint32_t>(plane * sizeof(T));
+  auto site_off = [&](int y, int x) {
+    return (static_cast<uint32_t>(y) * static_cast<uint32_t>(nx) + x) * sizeof(T);
+  };
+  auto wrap_y = [&](int y) { return WALLY ? clampi(y, 0, ny - 1) : pmod(y, ny); };
+  const uint32_t off_s = site_off(wrap_y(y0 + wv - 1), pmod(x0 + lane, nx));
+  const int64_t pz = static_cast<int64_t>(z) * plane;
+  // the plane that direction c_z = +1, -1 comes from
+  const int64_t pm = static_cast<int64_t>(z > 0 ? z - 1 : nz - 1) * plane;
+  const int64_t pp = static_cast<int64_t>(z + 1 < nz ? z + 1 : 0) * plane;
+
+  const bool interior = wv >= 1 && wv <= TY;
+  if (__builtin_amdgcn_readfirstlane(static_cast<int>(interior)) != 0) {
+    RawHalo rm[1], rp[1];
+    RawOwn r0[1];
+    P::template fetch<false, 1>(a, pm, off_s, plane_bytes, rm);
+    P::template fetch<true, 1>(a, pz, off_s, plane_bytes, r0);
+    P::template fetch<false, 1>(a, pp, off_s, plane_bytes, rp);
+    C g0[Q], gv[3];  // the own plane's values; those along the column
+    Carry cd[1], other;
+    if constexpr (KS) {
+      sgl[0][wv][lane + 1] = P::scalar(rm[0]);
+      sgl[1][wv][lane + 1] = P::scalar(r0[0]);
+      sgl[2][wv][lane + 1] = P::scalar(rp[0]);
+    }
+    auto stage = [&](auto CZ, const C (&g)[Q]) __attribute__((always_inline)) {
+      static_for<NP>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (L::cz(i) == decltype(CZ)::value) lds[i][wv][lane + 1] = g[i];
+      });
+    };
+    {
+      C g[Q];
+      P::template source<false, kSelAll>(a, rm[0], g, other);
+      stage(std::integral_constant<int, 1>{}, g);
+      gv[1] = g[L::kUp];
+    }
+    P::template source<true, kSelAll>(a, r0[0], g0, cd[0]);
+    stage(std::integral_constant<int, 0>{}, g0);
+    gv[0] = g0[L::kRest];
+    {
+      C g[Q];
+      P::template source<false, kSelAll>(a, rp[0], g, other);
+      stage(std::integral_constant<int, -1>{}, g);
+      gv[2] = g[L::kDown];
+    }
+    __syncthreads();
+    const int xd = x0 + lane, yd = y0 + wv - 1;
+    const bool wall_lo = WALLY && yd == 0, wall_hi = WALLY && yd == ny - 1;
+    Sums<C> acc[1];
+    zero(acc[0]);
+    auto gather = [&](auto CZ) __attribute__((always_inline)) {
+      static_for<Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (L::cz(i) == decltype(CZ)::value) {
+          C v;
+          if constexpr (i < NP) {
+            v = lds[i][wv - L::cy(i)][lane + 1 - L::cx(i)];
+            if constexpr (WALLY && L::cy(i) == 1) v = wall_lo ? C(0) : v;
+            if constexpr (WALLY && L::cy(i) == -1) v = wall_hi ? C(0) : v;
+          } else {
+            v = gv[i - NP];
+          }
+          accumulate<Q, i>(acc[0], v);
+        }
+      });
+    };
+    gather(std::integral_constant<int, 1>{});
+    gather(std::integral_constant<int, 0>{});
+    if constexpr (WALLY) {
+      // halfway bounce-back: the opposite value leaving the site itself
+      if (wall_lo)
+        static_for<Q>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          if constexpr (L::cy(i) == 1) accumulate<Q, i>(acc[0], g0[L::opp(i)]);
+        });
+      if (wall_hi)
+        static_for<Q>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          if constexpr (L::cy(i) == -1) accumulate<Q, i>(acc[0], g0[L::opp(i)]);
+        });
+    }
+    gather(std::integral_constant<int, -1>{});
+    const uint32_t off = (xd < nx && yd < ny) ? site_off(yd, xd) : plane_bytes;
+    if constexpr (KS) {
+      StencilRoll<C> sr;
+      sr.clear();
+      StencilOut<C> so[1];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        C n[3][3];
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int dx = 0; dx < 3; ++dx) n[dy][dx] = sgl[j][wv - 1 + dy][lane + dx];
+        so[0] = sr.plane(n);  // the third plane completes the site's
+      }
+      P::template finish<kCached, 1>(a, acc, cd, so, pz, off, plane_bytes);
+    } else {
+      P::template finish<kCached, 1>(a, acc, cd, pz, off, plane_bytes);
+    }
+  } else {
+    // a y-halo row, and one x-halo column site per lane (lanes 0 .. R - 1)
+    auto halo = [&](auto RS, auto CS) __attribute__((always_inline)) {
+      constexpr int rs = decltype(RS)::value, cs = decltype(CS)::value;
+      const bool do_col = lane < R;
+      const int hcol = wv == 0 ? 0 : W - 1;
+      const uint32_t off_h = do_col ? site_off(wrap_y(y0 - 1 + lane),
+                                               pmod(wv == 0 ? x0 - 1 : x0 + 64, nx))
+                                    : plane_bytes;
+      RawHalo row[3][1], col[3][1];
+      const int64_t from[3] = {pm, pz, pp};
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        P::template fetch<false, 1>(a, from[j], off_s, plane_bytes, row[j]);
+        P::template fetch<false, 1>(a, from[j], off_h, plane_bytes, col[j]);
+      }
+      static_for<3>([&](auto J) {
+        constexpr int j = decltype(J)::value, cz = 1 - j;
+        C g[Q];
+        Carry c;
+        P::template source<false, rs>(a, row[j][0], g, c);
+        static_for<NP>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          if constexpr (selected_dir<Q, rs>(i) && L::cz(i) == cz) lds[i][wv][lane + 1] = g[i];
+        });
+        if constexpr (KS) {
+          sgl[j][wv][lane + 1] = P::scalar(row[j][0]);
+          if (do_col) sgl[j][lane][hcol] = P::scalar(col[j][0]);
+        }
+        P::template source<false, cs>(a, col[j][0], g, c);
+        if (do_col)
+          static_for<NP>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (selected_dir<Q, cs>(i) && L::cz(i) == cz) lds[i][lane][hcol] = g[i];
+          });
+      });
+      __syncthreads();
+    };
+    if (wv == 0)
+      halo(std::integral_constant<int, kSelUp>{}, std::integral_constant<int, kSelRight>{});
+    else
+      halo(std::integral_constant<int, kSelDown>{}, std::integral_constant<int, kSelLeft>{});
+  }
+}
+
 // LDS bytes of one workgroup: NP staged values x (TY+2) rows x (64 S + 2)
 // columns, plus the x-halo column buffer (NP x 2 x (TY+2)); a stencil's
 // scalar takes one more such slot
@@ -490,6 +682,13 @@ hipError_t launch_march_s(const StepArgs& a, hipStream_t stream) {
   }
 }
 
+template <class P, bool WALLY>
+hipError_t launch_slab(const StepArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((slab_kernel<P, kSlabRows, WALLY>), dim3(a.tiles_x * a.tiles_y * a.zchunks),
+                     dim3(64 * (kSlabRows + 2)), 0, stream, a);
+  return hipGetLastError();
+}
+
 // one, two or three consecutive x-sites per lane (a.lane_sites); the two-
 // and three-site forms exist for tiles of up to 8 rows (taller ones measured
 // slower), the three-site form (192-wide tiles) for 4-byte storage
@@ -505,6 +704,9 @@ hipError_t launch_march(const StepArgs& a, hipStream_t stream) {
     return hipErrorInvalidValue;
   }
   if (a.lane_sites != 1) return hipErrorInvalidValue;
+  if constexpr (P::kSlabForms && TY == kSlabRows)
+    if (a.slab) return launch_slab<P, WALLY>(a, stream);
+  if (a.slab) return hipErrorInvalidValue;
   if constexpr (P::kCachedForms && march_cached(1, TY))
     if (a.cached) return launch_march_s<P, TY, WALLY, 1, kCached>(a, stream);
   return launch_march_s<P, TY, WALLY, 1>(a, stream);

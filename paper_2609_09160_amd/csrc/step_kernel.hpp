@@ -255,6 +255,8 @@ struct Forward {
   // forms with plain stores, for states that fit the last-level cache (16-bit
   // D3Q27h keeps the one form, whose words the other would not repeat)
   static constexpr bool kCachedForms = !FNEXT && !(FULL && S::kNeq);
+  // no one-plane forms of 16-bit storage: they do not repeat the march's words
+  static constexpr bool kSlabForms = ST == kF64 || ST == kF32;
   // raw (still encoded) moments and force of one site, fetched a plane ahead;
   // with a time-dependent force also phi(t+1) (the stencil's scalar) and,
   // with variable properties, phi(t)
