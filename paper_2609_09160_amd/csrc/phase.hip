@@ -44,9 +44,14 @@ __device__ __forceinline__ C inv_norm_eps(C g2, C eps) {
 // per-site record staged by the phase update: the total phase flux
 // V = phi u + lambda phi (1 - phi) grad(phi) / (|grad phi| + eps) (advection plus
 // interface compression, so that Eq. (2) reads phi' = phi - div(V) + D lap(phi))
-// and phi itself, interleaved so that a neighbour is one 4-wide load
+// and phi itself.  In LDS the four lie in arrays of their own, so that a wave's
+// reads of one of them take consecutive banks: a neighbour needs only some (v_x
+// where dx is not 0, v_y where dy is not 0), and the compiler then reads
+// interleaved records piece by piece, 16 bytes from lane to lane, four lanes to
+// a bank (36% of the kernel's cycles at 256^3 FP32; us per two-component step,
+// interleaved / apart: 256^3 525 / 506, FP16 399 / 385, 128^3 FP64 165 / 158).
 template <typename C>
-struct alignas(4 * sizeof(C)) Rec {
+struct Rec {
   C vx, vy, vz, phi;
 };
 
@@ -61,7 +66,7 @@ struct alignas(4 * sizeof(C)) Rec {
 // corrected, once phi_0 is known, by the weight sum (36) times the
 // difference, so FP32 adds only small differences.
 // 16 rows: the record ring and the phi halo are a smaller share of the tile
-// than with 8 (measured 1% faster for the whole two-component step at 256^3)
+// than with 8 (256^3 FP32 506 us for the whole two-component step, 8 rows 537)
 constexpr int kUpdRows = 16;
 constexpr int kLowRows = 4;
 // Loads ahead of use in the staged marches.  Iterations run in groups of
@@ -103,7 +108,7 @@ __global__ void __launch_bounds__(64 * ROWS) phase_kernel(
   constexpr int PERP = (NP + NT - 1) / NT, PERV = (NV + NT - 1) / NT;
   constexpr int KZ = kPlaneK;
   __shared__ C tp[2][NP];
-  __shared__ Rec<C> tv[2][NV];
+  __shared__ C tv[2][4][NV];  // v_x, v_y, v_z, phi
   const int lane = threadIdx.x & 63, wy = threadIdx.x >> 6;
   int b = static_cast<int>(blockIdx.x);
   const int tx = b % tiles_x;
@@ -210,7 +215,13 @@ __global__ void __launch_bounds__(64 * ROWS) phase_kernel(
     if (q >= z0 + 1) {
 #pragma unroll
       for (int k = 0; k < PERV; ++k)
-        if (vact[k]) tv[q & 1][threadIdx.x + k * NT] = rv[k];
+        if (vact[k]) {
+          const int e = threadIdx.x + k * NT;
+          tv[q & 1][0][e] = rv[k].vx;
+          tv[q & 1][1][e] = rv[k].vy;
+          tv[q & 1][2][e] = rv[k].vz;
+          tv[q & 1][3][e] = rv[k].phi;
+        }
     }
     __syncthreads();
     if (q <= z1 + 1) {
@@ -249,17 +260,17 @@ __global__ void __launch_bounds__(64 * ROWS) phase_kernel(
     }
     if (q >= z0 + 1) {
       // records V(q - 2): destination q - 3 completes
-      const Rec<C>* t = tv[q & 1];
+      const C(&t)[4][NV] = tv[q & 1];
       C vx[3][3], vy[3][3], vz[3][3], ph[3][3];
 #pragma unroll
       for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx) {
-          const Rec<C> n = t[(wy + dy) * VX + lane + dx];
-          vx[dy][dx] = n.vx;
-          vy[dy][dx] = n.vy;
-          vz[dy][dx] = n.vz;
-          ph[dy][dx] = n.phi;
+          const int e = (wy + dy) * VX + lane + dx;
+          vx[dy][dx] = t[0][e];
+          vy[dy][dx] = t[1][e];
+          vz[dy][dx] = t[2][e];
+          ph[dy][dx] = t[3][e];
         }
       const C own = ph[1][1];
       // window sums of the records: a = sum k1 k1 (c_x v_x + c_y v_y) and
