@@ -251,15 +251,14 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
   if (h->two_phase) f.read += c, f.write += 3 * c, f.streams += 1;
   if (adjoint) f.read = 22 * c, f.write = 13 * c, f.streams = 13, f.stencil = false;
   // fitted to the times of 250 to 900 launch shapes on each of 67 grids (8 x
-  // 29 x 168 to 512^3), per velocity set and compute type; the 27h FP64 one
-  // is scaled from its FP32 one
+  // 29 x 168 to 512^3), per velocity set and compute type
   const bool f64 = f.storage == LBF_F64;
   if (f.Q == LBF_D3Q19) {
     f.l0 = 0.45, f.l1 = f64 ? 0.15 : 0.07, f.busy = f64 ? 0.19 : 0.09;
   } else if (f.Q == LBF_D3Q27) {
     f.l0 = f64 ? 0.8 : 0.6, f.l1 = f64 ? 0.185 : 0.1, f.busy = f64 ? 0.3 : 0.135;
   } else {
-    f.l0 = f64 ? 1.5 : 1.15, f.l1 = f64 ? 0.1 : 0.045, f.busy = f64 ? 0.4 : 0.175;
+    f.l0 = f64 ? 1.3 : 1.15, f.l1 = f64 ? 0.2 : 0.045, f.busy = f64 ? 0.37 : 0.175;
   }
   // the stencils of the two-component step, and the adjoint's 22 values per
   // site, by the same measure
@@ -368,13 +367,17 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   return best;
 }
 
-// Modelled time of the one-plane form, in march_us's terms: its workgroups take
-// 12.2 busy us each one after the other on a CU, and it has no chain of planes
-// before the first of them.
+// Modelled time of the one-plane form, in march_us's terms: a CU's workgroups one
+// after the other, 13 busy us each (16 with a force field, 17.5 with the stencils
+// of the two-component step), and no chain of planes before the first of them.
+// Fitted to both forms' times on 7 grids from 32^3 to 40 x 180 x 100 for each of
+// 15 forms: the choice takes 1.007 times as long as the better of the two in the
+// geometric mean, and no form has a march of those grids replaced by a one-plane
+// step that takes more than 1.13 times as long.
 double slab_us(const lbfast_ctx* h, const MarchForm& f) {
   const double w = static_cast<double>(ceil_div(h->p.nx, 64) * ceil_div(h->p.ny, lbf::kSlabRows)) *
                    static_cast<double>(h->p.nz);
-  return 12.2 * f.busy * std::ceil(w / 256.0) - 1.35;
+  return (f.stencil ? 17.5 : h->Ffield ? 16.0 : 13.0) * f.busy * std::ceil(w / 256.0) - 1.0;
 }
 
 // the one-plane form in place of a march that is modelled to take `march` us
@@ -440,9 +443,10 @@ void width_launch(lbfast_ctx* h) {
 //   * variable density or viscosity: one site per lane (two spill; 256^3 FP32
 //     0.80 ms against 0.57);
 //   * 6 rows at most with three sites (8 spill with a force field: 192^3 143 us
-//     against 199), and, for the two-component step with D3Q27 and D3Q27h, with
-//     two sites or FP64 (256^3 FP32 645 us with two sites and 8 rows, 542 with
-//     one; 192^3 FP64 938 us with 8 rows, 654 with 6).
+//     against 199), for the two-component step with D3Q27 and D3Q27h with two
+//     sites or FP64 (256^3 FP32 645 us with two sites and 8 rows, 542 with one;
+//     192^3 FP64 938 us with 8 rows, 654 with 6), and for D3Q27h FP64 with a
+//     force field (8 spill: 130^3 181 us, 144 with 6).
 void model_launch(lbfast_ctx* h) {
   const int64_t nx = h->p.nx;
   const bool f64 = h->p.storage == LBF_F64;
@@ -464,7 +468,8 @@ void model_launch(lbfast_ctx* h) {
     if (is_16bit(h->p.storage) && !one_only && S != (two ? 2 : 1)) continue;
     for (int ty : lbf::kTileRowsSupported) {
       if (!shape_built(h, S, ty)) continue;
-      if (ty > 6 && (S == 3 || (h->two_phase && h->p.lattice != LBF_D3Q19 && (S == 2 || f64))))
+      if (ty > 6 && (S == 3 || (h->two_phase && h->p.lattice != LBF_D3Q19 && (S == 2 || f64)) ||
+                     (f64 && h->p.lattice == LBF_D3Q27H && h->Ffield)))
         continue;
       if (f64 && !one_only && !fits_cache(h) && (two ? (S != 2 || ty != 4) : S != 1)) continue;
       double t;
