@@ -342,9 +342,10 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
     consider(by_width);
   } else if (!fits && cols >= 256) {
     // a column for every CU: about 512 workgroups in chunks of >= 64 planes
-    // (512^3 FP32: 2.00 ms, one chunk per column 2.02), FP64 1024 (3.91 ms,
-    // one chunk per column 4.35)
-    const int64_t target = f.storage == LBF_F64 ? 1024 : 512;
+    // (512^3 FP32: 2.00 ms, one chunk per column 2.02), FP64 with two sites
+    // per lane 1024 (3.91 ms, one chunk per column 4.35; D3Q27h with one site
+    // and 8 rows 4.70 ms, one chunk per column 4.07)
+    const int64_t target = f.storage == LBF_F64 && S == 2 ? 1024 : 512;
     const int64_t zc = ceil_div(nz, std::min(std::max<int64_t>(1, target / cols),
                                              std::max<int64_t>(1, nz / 64)));
     consider(even_only && zc < nz ? zc + zc % 2 : zc);
@@ -437,9 +438,10 @@ void width_launch(lbfast_ctx* h) {
 //     of the stored 16-bit words after ten steps, and a run's values should not
 //     depend on the other extents (see keeps_parity for what else it keeps);
 //   * FP64: one site per lane for D3Q27 and D3Q27h (two spill or leave one
-//     short workgroup per CU), and for D3Q19 beyond the cache two sites where
-//     the width suits them, with 4 rows (256^3: 497 us, 6 rows 575, one site
-//     and 14 rows 637);
+//     short workgroup per CU), and two sites where the width suits them, with
+//     4 rows, for D3Q19 beyond the cache (256^3: 497 us, 6 rows 575, one site
+//     and 14 rows 637) and for D3Q27 without a force field with a column for
+//     every CU (512^3 3.78 ms, one site and 8 rows 3.95; 256^3 0.545, 0.530);
 //   * variable density or viscosity: one site per lane (two spill; 256^3 FP32
 //     0.80 ms against 0.57);
 //   * 6 rows at most with three sites (8 spill with a force field: 192^3 143 us
@@ -452,8 +454,10 @@ void model_launch(lbfast_ctx* h) {
   const bool f64 = h->p.storage == LBF_F64;
   const bool two = nx % 2 == 0 && nx >= 128 &&
                    ceil_div(nx, 128) * 128 - nx <= ceil_div(nx, 64) * 64 - nx;
+  const bool wide27 = f64 && h->p.lattice == LBF_D3Q27 && two && !h->Ffield && !h->two_phase &&
+                      !fits_cache(h) && ceil_div(nx, 128) * ceil_div(h->p.ny, 4) >= 256;
   const bool one_only = (h->two_phase && variable_properties(h)) ||
-                        (f64 && h->p.lattice != LBF_D3Q19);
+                        (f64 && h->p.lattice != LBF_D3Q19 && !wide27);
   h->auto_slab = false;
   if (keeps_rows(h)) {
     h->auto_sites = h->lane_sites;
