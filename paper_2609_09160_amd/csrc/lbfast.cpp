@@ -545,16 +545,21 @@ int adjoint_rows(const lbfast_ctx* h, const MarchForm& f, int sites) {
 
 // Block order: a contiguous range of tiles per XCD where the state is in the
 // cache and large enough for its halo lines to matter (201 x 97 x 113 FP32
-// 38 us against 47 in the hardware's order; 64^3 10.0 against 9.0), and for
-// FP64 with more columns than CUs (512^3 D3Q19 3.91 ms against 5.55).
-// Elsewhere the hardware's order: marches of one wave of workgroups keep
+// 38 us against 47 in the hardware's order; 64^3 10.0 against 9.0).  Beyond the
+// cache for the FP64 step of D3Q19 (13 grids from 180 x 250 x 120 to 320^3 4%
+// faster, with a force field too: 256^3 481 us against 537, 250^3 506 and 531,
+// 320^3 1013 and 1035; 275 x 245 x 97 4% slower), and otherwise in FP64 with
+// more columns than CUs (512^3 D3Q19 3.91 ms against 5.55; with fewer columns
+// D3Q27 and D3Q27h are as fast in either on 13 grids, but 320^3 1313 us against
+// 1115).  Elsewhere the hardware's order: marches of one wave of workgroups keep
 // step by themselves, and several waves lose about 10% in the other.
-bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y) {
+bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y, bool adjoint = false) {
   if (h->block_order != 0) return h->block_order == 2;
   // measured 6% slower for 16-bit D3Q27h at 267 x 122 x 127
   if (h->two_phase || keeps_rows(h)) return false;
   if (fits_cache(h)) return cache_matters(h);
-  return h->p.storage == LBF_F64 && static_cast<int64_t>(tiles_x) * tiles_y > 256;
+  return h->p.storage == LBF_F64 && ((h->p.lattice == LBF_D3Q19 && !adjoint) ||
+                                     static_cast<int64_t>(tiles_x) * tiles_y > 256);
 }
 
 int check_handle(lbfast_t h) {
@@ -1373,7 +1378,7 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   if (int rc = resolve_zchunk(h, adj_form, aa.lane_sites, adj_rows, &aa.tiles_x, &aa.tiles_y,
                               &aa.zchunks, &aa.zchunk))
     return rc;
-  aa.xcd_remap = contiguous_order(h, aa.tiles_x, aa.tiles_y);
+  aa.xcd_remap = contiguous_order(h, aa.tiles_x, aa.tiles_y, true);
   if (!h->adj_sites && !h->adj_rows && h->z_chunk == 0) {
     double march;
     (void)best_zchunk(h, adj_form, aa.lane_sites, adj_rows, &march);
