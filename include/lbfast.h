@@ -230,7 +230,8 @@ int lbfast_get_scales(lbfast_t h, float out[10]);
  * the shape of the least modelled time for the grid, storage and velocity set
  * (from there on it starts from 8 rows, F64 6, or 4 with two sites per lane).
  * The z-planes per workgroup follow the same model, down to one plane on
- * small grids; a z_chunk set here replaces it.
+ * small grids (with F32 and F64 storage in a kernel for single planes); a
+ * z_chunk set here replaces it.
  * Every shape computes the same formulas per site; the
  * tile heights are separately compiled, so results may differ between shapes
  * in the last bits (floating-point contraction), while one shape is bitwise
@@ -259,8 +260,8 @@ int lbfast_set_lane_sites(lbfast_t h, int sites);
  * forward pass, adjoint) are handed to the GPU's 8 XCDs (each with its own
  * L2), for the calls that follow: 0 = automatic (contiguous
  * tile ranges per XCD for states that fit the last-level cache but the
- * smallest, and for F64 grids of more than 256 tile columns, the hardware's
- * order otherwise),
+ * smallest, for larger F64 ones with LBF_D3Q19 (the step) or more than 256
+ * tile columns, the hardware's order otherwise),
  * 1 = the hardware's order (consecutive workgroups on the XCDs in turn),
  * 2 = a contiguous range of tiles per XCD.  A launch choice only: every
  * order computes bitwise the same results.  LBF_E_ARG for other values. */

@@ -332,7 +332,7 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   // in contiguous order, chunks that come out whole on each of the 8 XCDs
   // share all their halo lines there (201 x 97 x 113 D3Q27 FP32 with a field: 8
   // chunks 53 us, 9 chunks 60)
-  const bool whole = !f.stencil && cache_matters(h) && h->block_order != 1;
+  const bool whole = !f.stencil && cache_matters(h);
   auto consider = [&](int64_t zc) {
     double t = march_us(f, nx, ny, nz, fits, cached, S, ty, zc);
     if (whole && ceil_div(nz, zc) % 8 == 0) t *= 0.95;

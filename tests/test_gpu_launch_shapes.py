@@ -56,3 +56,21 @@ def test_states_beyond_the_cache(storage, shape, rows):
     for q in range(4):
         part = got[:, q * (nz // 4):(q + 1) * (nz // 4)]
         assert np.abs(part - want).max() <= tol
+
+
+@pytest.mark.parametrize("storage,Q,shape", [("f32", 27, (201, 97, 113)), ("f32", 19, (48, 48, 48)),
+                                             ("f64", 19, (152, 247, 151)), ("f16s", 19, (112, 112, 112))])
+def test_block_orders_agree_on_default_shapes(storage, Q, shape):
+    """The workgroup order does not move the default launch shape: automatic
+    and explicit orders give bitwise the same state."""
+    from paper_2609_09160_amd import Solver
+    m0 = inputs.random_state(shape, seed=sum(shape) + Q)
+    out = []
+    for order in (0, 1, 2):
+        s = Solver(shape, 0.65, lattice=Q, storage=storage)
+        s.set_block_order(order)
+        s.set_moments(m0)
+        s.step(3)
+        out.append(s.moments_host())
+        s.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
