@@ -1298,21 +1298,23 @@ int lbfast_forward_checkpointed(lbfast_t h, int64_t nsteps, int64_t every, void*
   }
   if (nsteps == 0) return LBF_OK;
   // The initial state is copied; a later checkpoint is written into its slot by
-  // the step that makes it, and read from there by the next one.
+  // the step that makes it, and read from there by the next one.  The other
+  // states go to the buffers that plain steps would put them in, so that a
+  // launch recorded before (a captured graph of an even number of steps) still
+  // finds the current state where it was.
   hipError_t e = hipMemcpyAsync(ck, h->buf[h->cur], bytes, hipMemcpyDeviceToDevice, h->stream);
   if (e != hipSuccess) return hip_fail(e, "checkpoint copy");
-  int cur = h->cur;
-  const void* at = h->buf[cur];
+  const void* at = h->buf[h->cur];
   for (int64_t t = 0; t < nsteps; ++t) {
     a.src = at;
     if ((t + 1) % every == 0 && t + 1 < nsteps)
       a.dst = ck + (t + 1) / every * bytes;
     else
-      a.dst = h->buf[cur ^= 1];
+      a.dst = h->buf[h->cur ^ 1];
     if (int rc = launch_forward(h, a)) return rc;
     at = a.dst;
+    h->cur ^= 1;
   }
-  h->cur = cur;
   return LBF_OK;
 }
 
