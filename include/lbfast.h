@@ -337,6 +337,10 @@ int lbfast_get_phase(lbfast_t h, void* phi, int dtype, int on_device);
  *   lambda_T_dev  10 x N, read only;
  *   gF_dev        3 x N, overwritten with dJ/dF;
  *   lambda0_dev   10 x N, overwritten with dJ/dm(0), or NULL.
+ * lambda_T_dev and lambda0_dev may be one array, and may lie in work_dev;
+ * lambda0_dev may also lie over the checkpoints or the force field, which are
+ * then lost.  (Arrays of their own on 16-byte boundaries are read and written
+ * in place, others are copied.)
  * Both calls are asynchronous on the handle's stream; the handle's own
  * state is left at m(T).  nsteps = 0 gives gF = 0 and lambda0 = lambda_T. */
 int lbfast_forward_checkpointed(lbfast_t h, int64_t nsteps, int64_t every, void* ckpt_dev);

@@ -588,6 +588,12 @@ bool is_device_ptr(const void* p) {
   return at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged;
 }
 
+// whether two arrays share memory (nullptr: no array)
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
+
 // launch geometry, relaxation, force and scales of the handle's step
 int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
   *a = lbf::StepArgs{};
@@ -1355,17 +1361,27 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   // work: recomputed states 1..every of a segment, then two adjoint buffers
   void* lam[2] = {work + every * bytes, work + (every + 1) * bytes};
   // The first adjoint step reads lambda_T and the last one writes lambda0 where
-  // they lie, unless they are one array and there is one step.
-  const char* lT = static_cast<const char*>(lambda_T_dev);
-  const char* l0 = static_cast<const char*>(lambda0_dev);
-  const bool apart = !l0 || nsteps > 1 || lT + bytes <= l0 || l0 + bytes <= lT;
-  const void* lam_src = lambda_T_dev;
-  if (!apart || reinterpret_cast<uintptr_t>(lT) % 16 != 0) {
+  // they lie, unless the memory is also used for something else meanwhile:
+  // lambda_T has to outlast the recomputation of the last segment, and lambda0
+  // is written by a step that still reads the first states and the force.
+  const int64_t nseg = (nsteps + every - 1) / every;
+  const size_t fbytes = 3 * static_cast<size_t>(N) * ce;
+  const size_t wbytes = lbfast_adjoint_work_bytes(h, every);
+  const bool lT_direct = reinterpret_cast<uintptr_t>(lambda_T_dev) % 16 == 0 &&
+                         !overlap(lambda_T_dev, bytes, work, wbytes) &&
+                         !overlap(lambda_T_dev, bytes, gF_dev, fbytes) &&
+                         !(nsteps == 1 && overlap(lambda_T_dev, bytes, lambda0_dev, bytes));
+  const bool l0_direct = lambda0_dev && reinterpret_cast<uintptr_t>(lambda0_dev) % 16 == 0 &&
+                         !overlap(lambda0_dev, bytes, work, wbytes) &&
+                         !overlap(lambda0_dev, bytes, ckpt_dev, nseg * bytes) &&
+                         !overlap(lambda0_dev, bytes, gF_dev, fbytes) &&
+                         !overlap(lambda0_dev, bytes, h->Ffield, fbytes);
+  if (!lT_direct) {
     e = hipMemcpyAsync(lam[0], lambda_T_dev, bytes, hipMemcpyDeviceToDevice, h->stream);
     if (e != hipSuccess) return hip_fail(e, "adjoint copy");
-    lam_src = lam[0];
   }
-  const bool l0_direct = l0 && reinterpret_cast<uintptr_t>(l0) % 16 == 0;
+  const void* lam_src = lT_direct ? lambda_T_dev : lam[0];
+  int cur = 0;
   lbf::StepArgs fa, aa;
   if (int rc = step_args(h, &fa)) return rc;
   aa = fa;
@@ -1386,7 +1402,6 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
     (void)best_zchunk(h, adj_form, aa.lane_sites, adj_rows, &march);
     if (slab_pays(h, adj_form, march)) slab_args(h, &aa);
   }
-  const int64_t nseg = (nsteps + every - 1) / every;
   const bool walls_y = h->p.bc[1] == LBF_WALLS;
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {
     const int64_t len = std::min(every, nsteps - seg * every);
@@ -1407,7 +1422,7 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
     }
     for (int64_t j = len - 1; j >= 0; --j) {  // sweep it backwards
       aa.src = lam_src;
-      aa.dst = lam_src == lam[0] ? lam[1] : lam[0];
+      aa.dst = lam[cur ^= 1];
       if (l0_direct && seg == 0 && j == 0) aa.dst = lambda0_dev;
       aa.state_old = state(j);
       aa.state_new = state(j + 1);
