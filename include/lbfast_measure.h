@@ -2,13 +2,15 @@
  * lbfast_measure.h -- measurement utilities of liblbfast.so.  They are not
  * part of the method: copy kernels of known size, used to calibrate hardware
  * traffic counters against the step and to measure the bandwidth ceiling
- * the step is set against.  Same status codes and error reporting as
- * lbfast.h.
+ * the step is set against, and what the library launches by default.  Same
+ * status codes and error reporting as lbfast.h.
  */
 #ifndef LBFAST_MEASURE_H_
 #define LBFAST_MEASURE_H_
 
 #include <stdint.h>
+
+#include "lbfast.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -52,6 +54,32 @@ int lbfast_planes_probe(const void* src, void* dst, int64_t n, int nplanes, void
  * step's access pattern against the layout of its 16-bit state. */
 int lbfast_zmarch_probe(const void* src, void* dst, int nx, int ny, int nz, int layout,
                         int zchunk, void* stream);
+
+/* What a new handle for `p` launches for one call, without a GPU:
+ * force_field != 0 with a per-site force field set, pp != NULL with the
+ * two-component variant enabled (not both). */
+enum {
+  LBF_LAUNCH_STEP = 0,    /* one step of lbfast_step */
+  LBF_LAUNCH_ADJOINT = 1  /* one adjoint step of lbfast_adjoint */
+};
+typedef struct lbfast_launch_info {
+  int32_t one_plane;    /* 1: one plane per workgroup, 0: a march along z */
+  int32_t lane_sites;   /* x-sites per lane */
+  int32_t tile_rows;
+  int32_t z_chunk;      /* planes per workgroup */
+  int32_t contiguous;   /* a contiguous range of tiles per XCD */
+  int32_t plain_stores; /* not past the last-level cache */
+  int64_t blocks;       /* workgroups, and work-items of each */
+  int64_t block_threads;
+} lbfast_launch_info;
+int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_phase_params* pp,
+                          int what, lbfast_launch_info* out);
+
+/* The form of the steps and adjoint steps that follow: LBF_FORM_AUTO as the
+ * library chooses, LBF_FORM_MARCH, or LBF_FORM_ONE_PLANE (F32 and F64 storage,
+ * up to 2^20 workgroups; launch shapes that were set do not apply to it). */
+enum { LBF_FORM_AUTO = 0, LBF_FORM_MARCH = 1, LBF_FORM_ONE_PLANE = 2 };
+int lbfast_set_form(lbfast_t h, int form);
 
 #ifdef __cplusplus
 }

@@ -19,6 +19,8 @@ LBF_D3Q19, LBF_D3Q27, LBF_D3Q27H = 19, 27, 270
 LBF_F64, LBF_F32, LBF_F16S, LBF_BF16S, LBF_F16SU = 0, 1, 2, 3, 4
 LBF_PERIODIC, LBF_WALLS = 0, 1
 LBF_ROUND_AUTO, LBF_ROUND_NEAREST, LBF_ROUND_STOCHASTIC = 0, 1, 2
+LBF_LAUNCH_STEP, LBF_LAUNCH_ADJOINT = 0, 1
+LBF_FORM_AUTO, LBF_FORM_MARCH, LBF_FORM_ONE_PLANE = 0, 1, 2
 ROUNDING = {"auto": LBF_ROUND_AUTO, "nearest": LBF_ROUND_NEAREST,
             "stochastic": LBF_ROUND_STOCHASTIC}
 
@@ -44,6 +46,13 @@ class LbfastPhaseParams(ctypes.Structure):
                 ("sigma", ctypes.c_double), ("width", ctypes.c_double),
                 ("diffusivity", ctypes.c_double), ("rho_l", ctypes.c_double),
                 ("rho_h", ctypes.c_double), ("tau_l", ctypes.c_double), ("tau_h", ctypes.c_double)]
+
+
+class LbfastLaunchInfo(ctypes.Structure):
+    _fields_ = [("one_plane", ctypes.c_int32), ("lane_sites", ctypes.c_int32),
+                ("tile_rows", ctypes.c_int32), ("z_chunk", ctypes.c_int32),
+                ("contiguous", ctypes.c_int32), ("plain_stores", ctypes.c_int32),
+                ("blocks", ctypes.c_int64), ("block_threads", ctypes.c_int64)]
 
 
 class LbfastError(RuntimeError):
@@ -97,6 +106,9 @@ def load():
         "lbfast_adjoint_work_bytes": ([vp, i64], ctypes.c_size_t),
         "lbfast_adjoint": ([vp, i64, i64, vp, vp, vp, vp, vp], i32),
         "lbfast_set_adjoint_launch": ([vp, i32, i32], i32),
+        "lbfast_set_form": ([vp, i32], i32),
+        "lbfast_default_launch": ([P, i32, ctypes.POINTER(LbfastPhaseParams), i32,
+                                   ctypes.POINTER(LbfastLaunchInfo)], i32),
     }
     for name, (args, res) in sig.items():
         if path != LIB_PATH and not hasattr(lib, name):

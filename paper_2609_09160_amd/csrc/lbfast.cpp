@@ -160,6 +160,7 @@ struct lbfast_ctx {
   uint64_t steps_done = 0;       // steps since create: seeds the stochastic rounding
   int adj_sites = 0, adj_rows = 0;  // adjoint launch shape (0: automatic)
   int block_order = 0;              // 0 automatic, 1 hardware order, 2 per-XCD ranges
+  int form = LBF_FORM_AUTO;         // march or one-plane form of the steps
 };
 
 namespace {
@@ -501,7 +502,41 @@ void model_launch(lbfast_ctx* h) {
   h->auto_slab = !is_16bit(h->p.storage) && slab_pays(h, f, t_best);
 }
 
-bool step_slab(const lbfast_ctx* h) { return !h->shape_set && h->z_chunk == 0 && h->auto_slab; }
+// problem and default launch shapes of a new handle
+void set_params(lbfast_ctx* h, const lbfast_params* p) {
+  h->p = *p;
+  h->N = p->nx * p->ny * p->nz;
+  width_launch(h);
+  model_launch(h);
+}
+
+// The shapes of a handle that has become a two-component one.
+void two_phase_launch(lbfast_ctx* h) {
+  // A shape chosen by the caller is kept where it can be.  The two-component
+  // step has one- and two-site forms of at most 8 rows,
+  // with one more LDS slot (phi(t+1)) than the one-component step.  With
+  // variable density or viscosity, one site per lane: the two-site form
+  // spills registers there (measured at 256^3 FP32: 0.80 ms against 0.57).
+  const bool one_site = h->lane_sites == 3 || (h->lane_sites == 2 && variable_properties(h));
+  const bool reshape = one_site || h->tile_rows > 8 ||
+                       lds_bytes(h->p.lattice, h->p.storage, h->tile_rows, h->lane_sites,
+                                 true) > kLdsLimit;
+  if (one_site) h->lane_sites = 1;
+  if (reshape) {
+    h->tile_rows = 4;
+    for (int ty : {8, 6})
+      if (lds_bytes(h->p.lattice, h->p.storage, ty, h->lane_sites, true) <= kLdsLimit) {
+        h->tile_rows = ty;
+        break;
+      }
+  }
+  model_launch(h);
+}
+
+bool step_slab(const lbfast_ctx* h) {
+  if (h->form != LBF_FORM_AUTO) return h->form == LBF_FORM_ONE_PLANE;
+  return !h->shape_set && h->z_chunk == 0 && h->auto_slab;
+}
 
 // launch geometry of the one-plane form
 void slab_args(const lbfast_ctx* h, lbf::StepArgs* a) {
@@ -644,6 +679,30 @@ int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
     a->nu_l = (h->pp.tau_l - 0.5) / 3.0;
     a->nu_h = (h->pp.tau_h - 0.5) / 3.0;
   }
+  return LBF_OK;
+}
+
+// Launch geometry of the adjoint step, which reads 22 values per destination
+// site: by default one site per lane and 8-row tiles (FP64: 6);
+// lbfast_set_adjoint_launch may choose two or three sites per lane with 4- or
+// 6-row tiles (FP32).
+int adjoint_launch(const lbfast_ctx* h, lbf::StepArgs* a, int* rows) {
+  const MarchForm f = march_form(h, true);
+  a->lane_sites = h->adj_sites ? h->adj_sites : 1;
+  *rows = adjoint_rows(h, f, a->lane_sites);
+  a->slab = 0;
+  a->cached = 0;
+  if (int rc = resolve_zchunk(h, f, a->lane_sites, *rows, &a->tiles_x, &a->tiles_y, &a->zchunks,
+                              &a->zchunk))
+    return rc;
+  a->xcd_remap = contiguous_order(h, a->tiles_x, a->tiles_y, true);
+  bool one_plane = h->form == LBF_FORM_ONE_PLANE;
+  if (h->form == LBF_FORM_AUTO && !h->adj_sites && !h->adj_rows && h->z_chunk == 0) {
+    double march;
+    (void)best_zchunk(h, f, a->lane_sites, *rows, &march);
+    one_plane = slab_pays(h, f, march);
+  }
+  if (one_plane) slab_args(h, a);
   return LBF_OK;
 }
 
@@ -791,10 +850,9 @@ int lbfast_create(const lbfast_params* p, void* stream, void* buf0, void* buf1, 
 
   lbfast_ctx* h = new (std::nothrow) lbfast_ctx();
   if (!h) return fail(LBF_E_NOMEM, "host allocation failed");
-  h->p = *p;
+  set_params(h, p);
   h->device = dev;
   h->stream = static_cast<hipStream_t>(stream);
-  h->N = p->nx * p->ny * p->nz;
   const size_t bytes = lbfast_buffer_bytes(p);
   for (int k = 0; k < 10; ++k) {
     h->scale[k] = (p->scale[k] != 0.0f) ? p->scale[k] : 1.0f;
@@ -807,9 +865,6 @@ int lbfast_create(const lbfast_params* p, void* stream, void* buf0, void* buf1, 
     for (int k = 0; k < 10; ++k) all = all && p->scale[k] != 0.0f;
     h->scales_fixed = all;
   }
-  width_launch(h);
-  model_launch(h);
-
   if (buf0) {
     h->buf[0] = buf0;
     h->buf[1] = buf1;
@@ -1145,6 +1200,65 @@ int lbfast_step(lbfast_t h, int64_t n) {
   return LBF_OK;
 }
 
+int lbfast_set_form(lbfast_t h, int form) {
+  g_err.clear();
+  if (int rc = check_handle(h)) return rc;
+  if (form != LBF_FORM_AUTO && form != LBF_FORM_MARCH && form != LBF_FORM_ONE_PLANE)
+    return fail(LBF_E_ARG, "unknown form %d", form);
+  if (form == LBF_FORM_ONE_PLANE) {
+    if (is_16bit(h->p.storage))
+      return fail(LBF_E_UNSUPPORTED, "16-bit storage has no one-plane form");
+    if (ceil_div(h->p.nx, 64) * ceil_div(h->p.ny, lbf::kSlabRows) * h->p.nz > (1 << 20))
+      return fail(LBF_E_UNSUPPORTED, "the one-plane form is for small grids");
+  }
+  h->form = form;
+  return LBF_OK;
+}
+
+int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_phase_params* pp,
+                          int what, lbfast_launch_info* out) {
+  g_err.clear();
+  if (int rc = validate(p)) return rc;
+  if (!out) return fail(LBF_E_ARG, "out is NULL");
+  if (force_field && pp) return fail(LBF_E_ARG, "the two-component variant has no force field");
+  if (pp && pp->struct_size != sizeof(lbfast_phase_params))
+    return fail(LBF_E_ARG, "phase params struct_size = %u, expected %zu", pp->struct_size,
+                sizeof(lbfast_phase_params));
+  if (pp && p->storage == LBF_F16SU)
+    return fail(LBF_E_UNSUPPORTED, "the two-component variant does not cover LBF_F16SU storage");
+  lbfast_ctx h;
+  set_params(&h, p);
+  if (force_field) {
+    h.Ffield = out;  // any address: only whether there is one counts here
+    model_launch(&h);
+  }
+  if (pp) {
+    h.pp = *pp;
+    h.two_phase = true;
+    two_phase_launch(&h);
+  }
+  lbf::StepArgs a;
+  if (int rc = step_args(&h, &a)) return rc;
+  int rows = step_rows(&h);
+  if (what == LBF_LAUNCH_ADJOINT) {
+    if (int rc = check_adjoint_args(&h, 1, 1)) return rc;
+    if (int rc = adjoint_launch(&h, &a, &rows)) return rc;
+  } else if (what != LBF_LAUNCH_STEP) {
+    return fail(LBF_E_ARG, "unknown launch %d", what);
+  }
+  if (a.slab) rows = lbf::kSlabRows;
+  *out = lbfast_launch_info{};
+  out->one_plane = a.slab;
+  out->lane_sites = a.lane_sites;
+  out->tile_rows = rows;
+  out->z_chunk = a.zchunk;
+  out->contiguous = a.xcd_remap;
+  out->plain_stores = a.slab || a.cached;
+  out->blocks = static_cast<int64_t>(a.tiles_x) * a.tiles_y * a.zchunks;
+  out->block_threads = 64 * (rows + 2);
+  return LBF_OK;
+}
+
 int lbfast_enable_two_phase(lbfast_t h, const lbfast_phase_params* pp) {
   g_err.clear();
   if (int rc = check_handle(h)) return rc;
@@ -1190,25 +1304,7 @@ int lbfast_enable_two_phase(lbfast_t h, const lbfast_phase_params* pp) {
   h->pp = *pp;
   h->two_phase = true;
   h->pcur = 0;
-  // A shape chosen by the caller is kept where it can be.  The two-component
-  // step has one- and two-site forms of at most 8 rows,
-  // with one more LDS slot (phi(t+1)) than the one-component step.  With
-  // variable density or viscosity, one site per lane: the two-site form
-  // spills registers there (measured at 256^3 FP32: 0.80 ms against 0.57).
-  const bool one_site = h->lane_sites == 3 || (h->lane_sites == 2 && variable_properties(h));
-  const bool reshape = one_site || h->tile_rows > 8 ||
-                       lds_bytes(h->p.lattice, h->p.storage, h->tile_rows, h->lane_sites,
-                                 true) > kLdsLimit;
-  if (one_site) h->lane_sites = 1;
-  if (reshape) {
-    h->tile_rows = 4;
-    for (int ty : {8, 6})
-      if (lds_bytes(h->p.lattice, h->p.storage, ty, h->lane_sites, true) <= kLdsLimit) {
-        h->tile_rows = ty;
-        break;
-      }
-  }
-  model_launch(h);
+  two_phase_launch(h);
   // F(0) of phi = 0: the body force alone
   lbf::PhaseArgs pa = phase_args(h);
   pa.phi_out = h->phi[0];
@@ -1396,22 +1492,8 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   if (int rc = step_args(h, &fa)) return rc;
   aa = fa;
   aa.gF = gF_dev;
-  // The adjoint step reads 22 values per destination site: by default one
-  // site per lane and 8-row tiles (FP64: 6); lbfast_set_adjoint_launch may
-  // choose two or three sites per lane with 4- or 6-row tiles (FP32)
-  aa.lane_sites = h->adj_sites ? h->adj_sites : 1;
-  const MarchForm adj_form = march_form(h, true);
-  const int adj_rows = adjoint_rows(h, adj_form, aa.lane_sites);
-  aa.slab = 0;
-  if (int rc = resolve_zchunk(h, adj_form, aa.lane_sites, adj_rows, &aa.tiles_x, &aa.tiles_y,
-                              &aa.zchunks, &aa.zchunk))
-    return rc;
-  aa.xcd_remap = contiguous_order(h, aa.tiles_x, aa.tiles_y, true);
-  if (!h->adj_sites && !h->adj_rows && h->z_chunk == 0) {
-    double march;
-    (void)best_zchunk(h, adj_form, aa.lane_sites, adj_rows, &march);
-    if (slab_pays(h, adj_form, march)) slab_args(h, &aa);
-  }
+  int adj_rows = 0;
+  if (int rc = adjoint_launch(h, &aa, &adj_rows)) return rc;
   const bool walls_y = h->p.bc[1] == LBF_WALLS;
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {
     const int64_t len = std::min(every, nsteps - seg * every);

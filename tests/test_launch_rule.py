@@ -1,0 +1,51 @@
+"""What the library launches by default, form by form (no GPU needed)."""
+import ctypes
+
+import pytest
+
+from launch_util import CONTRAST, EQUAL, default_launch
+from paper_2609_09160_amd import _lib
+
+SMALL = [(1, 1, 1), (5, 3, 1), (64, 4, 2), (65, 5, 3), (127, 2, 5), (32, 32, 32)]
+
+
+@pytest.mark.parametrize("shape", SMALL)
+@pytest.mark.parametrize("Q", [19, 27, "27h"])
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+def test_small_grids_take_the_one_plane_form(shape, Q, storage):
+    kinds = [{}, {"field": True}, {"phase": EQUAL}, {"phase": CONTRAST}]
+    if Q != "27h":
+        kinds.append({"field": True, "what": _lib.LBF_LAUNCH_ADJOINT})
+    for kind in kinds:
+        got = default_launch(shape, Q, storage, **kind)
+        assert got["one_plane"] == 1 and got["z_chunk"] == 1 and got["lane_sites"] == 1, kind
+        nx, ny, nz = shape
+        assert got["blocks"] == -(-nx // 64) * -(-ny // got["tile_rows"]) * nz
+
+
+@pytest.mark.parametrize("storage", ["f16s", "bf16s", "f16su"])
+@pytest.mark.parametrize("shape", SMALL)
+def test_16bit_storage_marches(storage, shape):
+    assert default_launch(shape, 19, storage)["one_plane"] == 0
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("what", [_lib.LBF_LAUNCH_STEP, _lib.LBF_LAUNCH_ADJOINT])
+def test_large_grids_march(storage, what):
+    assert default_launch((192, 192, 192), 19, storage, field=True, what=what)["one_plane"] == 0
+
+
+def test_what_cannot_be_launched_is_refused():
+    out = _lib.LbfastLaunchInfo()
+    lib = _lib.load()
+
+    def rc(what, field=0, **kw):
+        p = _lib.make_params((8, 8, 8), 0.8, **kw)
+        return lib.lbfast_default_launch(ctypes.byref(p), field, None, what, ctypes.byref(out))
+
+    assert rc(_lib.LBF_LAUNCH_STEP) == _lib.LBF_OK
+    assert rc(99) == _lib.LBF_E_ARG
+    assert rc(_lib.LBF_LAUNCH_ADJOINT, storage="f16s") == _lib.LBF_E_UNSUPPORTED
+    assert rc(_lib.LBF_LAUNCH_ADJOINT, lattice="27h") == _lib.LBF_E_UNSUPPORTED
+    assert lib.lbfast_default_launch(None, 0, None, 0, ctypes.byref(out)) == _lib.LBF_E_ARG
+    assert lib.lbfast_set_form(None, 1) == _lib.LBF_E_ARG
