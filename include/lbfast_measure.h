@@ -60,7 +60,14 @@ int lbfast_zmarch_probe(const void* src, void* dst, int nx, int ny, int nz, int 
  * two-component variant enabled (not both). */
 enum {
   LBF_LAUNCH_STEP = 0,    /* one step of lbfast_step */
-  LBF_LAUNCH_ADJOINT = 1  /* one adjoint step of lbfast_adjoint */
+  LBF_LAUNCH_ADJOINT = 1, /* one adjoint step of lbfast_adjoint */
+  /* lbfast_set_moments from and lbfast_get_moments into device arrays: blocks
+   * and block_threads of the one launch for the whole state, blocks = 0 where
+   * it is too large for one and goes plane by plane */
+  LBF_LAUNCH_SET_F64 = 4,
+  LBF_LAUNCH_SET_F32 = 5,
+  LBF_LAUNCH_GET_F64 = 6,
+  LBF_LAUNCH_GET_F32 = 7
 };
 typedef struct lbfast_launch_info {
   int32_t one_plane;    /* 1: one plane per workgroup, 0: a march along z */

@@ -57,7 +57,7 @@ hipError_t launch_adjoint(int Q, int storage, int tile_rows, bool walls_y, const
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kConvertThreads;
 
 __global__ void zero_kernel(uint32_t* __restrict__ p, int64_t n) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; i < n;
@@ -528,23 +528,12 @@ hipError_t decode_st(int user_dtype, const void* buf, void* plane, int64_t N, in
   return hipGetLastError();
 }
 
-// Blocks of kThreads threads, `per` items each
-hipError_t one_shot_grid(int64_t n, int64_t per, dim3* grid) {
-  const int64_t b = (n + kThreads * per - 1) / (kThreads * per);
-  if (b > 0x7fffffff) return hipErrorInvalidValue;
-  *grid = dim3(static_cast<unsigned>(b));
-  return hipSuccess;
-}
-
 // Arrays of more than half the 256 MB last-level cache are written past it:
 // what is read next is no longer there anyway.
 constexpr int64_t kStreamBytes = 128 << 20;
 
 template <typename From, typename To>
-hipError_t convert_flat(const void* src, void* dst, int64_t n, hipStream_t st) {
-  constexpr int64_t V = 16 / sizeof(To);
-  dim3 grid;
-  if (hipError_t e = one_shot_grid(n, V, &grid); e != hipSuccess) return e;
+hipError_t convert_flat(const void* src, void* dst, int64_t n, dim3 grid, hipStream_t st) {
   const From* a = static_cast<const From*>(src);
   To* b = static_cast<To*>(dst);
   if (n * static_cast<int64_t>(sizeof(To)) > kStreamBytes)
@@ -555,13 +544,11 @@ hipError_t convert_flat(const void* src, void* dst, int64_t n, hipStream_t st) {
 }
 
 template <int ST, typename U>
-hipError_t decode_all_16(const void* buf, void* user, int64_t N, const float* scale,
+hipError_t decode_all_16(const void* buf, void* user, int64_t N, const float* scale, dim3 grid,
                          hipStream_t st) {
   using T = typename Storage<ST>::T;
   const int64_t V = N % 2 ? 1 : 2;
   const int nt = 10 * N * static_cast<int64_t>(sizeof(U)) > kStreamBytes;
-  dim3 grid;
-  if (hipError_t e = one_shot_grid(N, V, &grid); e != hipSuccess) return e;
   const T* a = static_cast<const T*>(buf);
   U* b = static_cast<U*>(user);
   if (V == 2)
@@ -575,11 +562,9 @@ hipError_t decode_all_16(const void* buf, void* user, int64_t N, const float* sc
 
 template <int ST, typename U>
 hipError_t encode_all_16(const void* user, void* buf, int64_t N, const float* inv,
-                         const float* fwd, hipStream_t st) {
+                         const float* fwd, dim3 grid, hipStream_t st) {
   using T = typename Storage<ST>::T;
   const int64_t V = N % 2 ? 1 : 2;
-  dim3 grid;
-  if (hipError_t e = one_shot_grid(N, V, &grid); e != hipSuccess) return e;
   const U* a = static_cast<const U*>(user);
   T* b = static_cast<T*>(buf);
   if (V == 2)
@@ -720,25 +705,36 @@ hipError_t launch_decode(int storage, int user_dtype, const void* buf, void* pla
   }
 }
 
+int64_t whole_state_blocks(int storage, int user_dtype, bool to_user, int64_t N) {
+  const bool flat = storage == kF64 || storage == kF32;
+  const int64_t items = flat ? 10 * N : N;
+  const int64_t per = flat ? ((to_user ? user_dtype : storage) == kF64 ? 2 : 4) : (N % 2 ? 1 : 2);
+  const int64_t b = (items + kThreads * per - 1) / (kThreads * per);
+  return b * kThreads < (int64_t{1} << 32) ? b : 0;
+}
+
 hipError_t launch_encode_all(int storage, int user_dtype, const void* user, void* buf, int64_t N,
                              const float* inv_scale, const float* scale, hipStream_t s) {
   const bool u64 = user_dtype == kF64;
+  const int64_t blocks = whole_state_blocks(storage, user_dtype, false, N);
+  if (blocks == 0) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(blocks));
   switch (storage) {
     case kF64:
-      return u64 ? convert_flat<double, double>(user, buf, 10 * N, s)
-                 : convert_flat<float, double>(user, buf, 10 * N, s);
+      return u64 ? convert_flat<double, double>(user, buf, 10 * N, grid, s)
+                 : convert_flat<float, double>(user, buf, 10 * N, grid, s);
     case kF32:
-      return u64 ? convert_flat<double, float>(user, buf, 10 * N, s)
-                 : convert_flat<float, float>(user, buf, 10 * N, s);
+      return u64 ? convert_flat<double, float>(user, buf, 10 * N, grid, s)
+                 : convert_flat<float, float>(user, buf, 10 * N, grid, s);
     case kF16S:
-      return u64 ? encode_all_16<kF16S, double>(user, buf, N, inv_scale, scale, s)
-                 : encode_all_16<kF16S, float>(user, buf, N, inv_scale, scale, s);
+      return u64 ? encode_all_16<kF16S, double>(user, buf, N, inv_scale, scale, grid, s)
+                 : encode_all_16<kF16S, float>(user, buf, N, inv_scale, scale, grid, s);
     case kBF16S:
-      return u64 ? encode_all_16<kBF16S, double>(user, buf, N, inv_scale, scale, s)
-                 : encode_all_16<kBF16S, float>(user, buf, N, inv_scale, scale, s);
+      return u64 ? encode_all_16<kBF16S, double>(user, buf, N, inv_scale, scale, grid, s)
+                 : encode_all_16<kBF16S, float>(user, buf, N, inv_scale, scale, grid, s);
     case kF16SU:
-      return u64 ? encode_all_16<kF16SU, double>(user, buf, N, inv_scale, scale, s)
-                 : encode_all_16<kF16SU, float>(user, buf, N, inv_scale, scale, s);
+      return u64 ? encode_all_16<kF16SU, double>(user, buf, N, inv_scale, scale, grid, s)
+                 : encode_all_16<kF16SU, float>(user, buf, N, inv_scale, scale, grid, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -746,22 +742,25 @@ hipError_t launch_encode_all(int storage, int user_dtype, const void* user, void
 hipError_t launch_decode_all(int storage, int user_dtype, const void* buf, void* user, int64_t N,
                              const float* scale, hipStream_t s) {
   const bool u64 = user_dtype == kF64;
+  const int64_t blocks = whole_state_blocks(storage, user_dtype, true, N);
+  if (blocks == 0) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(blocks));
   switch (storage) {
     case kF64:
-      return u64 ? convert_flat<double, double>(buf, user, 10 * N, s)
-                 : convert_flat<double, float>(buf, user, 10 * N, s);
+      return u64 ? convert_flat<double, double>(buf, user, 10 * N, grid, s)
+                 : convert_flat<double, float>(buf, user, 10 * N, grid, s);
     case kF32:
-      return u64 ? convert_flat<float, double>(buf, user, 10 * N, s)
-                 : convert_flat<float, float>(buf, user, 10 * N, s);
+      return u64 ? convert_flat<float, double>(buf, user, 10 * N, grid, s)
+                 : convert_flat<float, float>(buf, user, 10 * N, grid, s);
     case kF16S:
-      return u64 ? decode_all_16<kF16S, double>(buf, user, N, scale, s)
-                 : decode_all_16<kF16S, float>(buf, user, N, scale, s);
+      return u64 ? decode_all_16<kF16S, double>(buf, user, N, scale, grid, s)
+                 : decode_all_16<kF16S, float>(buf, user, N, scale, grid, s);
     case kBF16S:
-      return u64 ? decode_all_16<kBF16S, double>(buf, user, N, scale, s)
-                 : decode_all_16<kBF16S, float>(buf, user, N, scale, s);
+      return u64 ? decode_all_16<kBF16S, double>(buf, user, N, scale, grid, s)
+                 : decode_all_16<kBF16S, float>(buf, user, N, scale, grid, s);
     case kF16SU:
-      return u64 ? decode_all_16<kF16SU, double>(buf, user, N, scale, s)
-                 : decode_all_16<kF16SU, float>(buf, user, N, scale, s);
+      return u64 ? decode_all_16<kF16SU, double>(buf, user, N, scale, grid, s)
+                 : decode_all_16<kF16SU, float>(buf, user, N, scale, grid, s);
     default: return hipErrorInvalidValue;
   }
 }

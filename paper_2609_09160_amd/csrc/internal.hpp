@@ -118,7 +118,12 @@ hipError_t launch_encode(int storage, int user_dtype, const void* plane, const v
 hipError_t launch_decode(int storage, int user_dtype, const void* buf, void* plane, int64_t N,
                          int k, const float* scale, hipStream_t stream);
 // The same for a whole state at once: user is a 10 x N array in device memory,
-// 16-byte aligned.
+// 16-byte aligned.  Workgroups (kConvertThreads each) of that launch, 0 if the
+// state is too large for it: HIP takes fewer than 2^32 work-items (from FP32 or
+// FP64 states of 8.6e8 sites on with doubles on the side that is written, and of
+// 1.7e9 with floats); the plane-wise launches loop and take any size.
+constexpr int kConvertThreads = 256;
+int64_t whole_state_blocks(int storage, int user_dtype, bool to_user, int64_t N);
 hipError_t launch_encode_all(int storage, int user_dtype, const void* user, void* buf, int64_t N,
                              const float* inv_scale, const float* scale, hipStream_t s);
 hipError_t launch_decode_all(int storage, int user_dtype, const void* buf, void* user, int64_t N,

@@ -1002,7 +1002,8 @@ int lbfast_set_moments(lbfast_t h, const void* m, int dtype, int on_device) {
   }
   void* dst = h->buf[h->cur];
   // device arrays in one pass (the vector accesses want 16-byte alignment)
-  const bool whole = on_device && reinterpret_cast<uintptr_t>(m) % 16 == 0;
+  const bool whole = on_device && reinterpret_cast<uintptr_t>(m) % 16 == 0 &&
+                     lbf::whole_state_blocks(h->p.storage, dtype, false, N) > 0;
   if (whole && e == hipSuccess)
     e = lbf::launch_encode_all(h->p.storage, dtype, m, dst, N, h->inv_scale, h->scale, h->stream);
   for (int k = 0; k < 10 && e == hipSuccess && !whole; ++k) {
@@ -1041,7 +1042,8 @@ int lbfast_get_moments(lbfast_t h, void* m, int dtype, int on_device) {
       return fail(LBF_E_NOMEM, "staging allocation failed");
     }
   }
-  const bool whole = on_device && reinterpret_cast<uintptr_t>(m) % 16 == 0;
+  const bool whole = on_device && reinterpret_cast<uintptr_t>(m) % 16 == 0 &&
+                     lbf::whole_state_blocks(h->p.storage, dtype, true, N) > 0;
   if (whole) e = lbf::launch_decode_all(h->p.storage, dtype, src, m, N, h->scale, h->stream);
   for (int k = 0; k < 10 && e == hipSuccess && !whole; ++k) {
     void* dst = on_device ? static_cast<void*>(static_cast<char*>(m) + k * pbytes) : staging;
@@ -1237,6 +1239,14 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
     h.two_phase = true;
     two_phase_launch(&h);
   }
+  *out = lbfast_launch_info{};
+  if (what >= LBF_LAUNCH_SET_F64 && what <= LBF_LAUNCH_GET_F32) {
+    out->blocks = lbf::whole_state_blocks(
+        p->storage, what == LBF_LAUNCH_SET_F64 || what == LBF_LAUNCH_GET_F64 ? LBF_F64 : LBF_F32,
+        what >= LBF_LAUNCH_GET_F64, h.N);
+    out->block_threads = lbf::kConvertThreads;
+    return LBF_OK;
+  }
   lbf::StepArgs a;
   if (int rc = step_args(&h, &a)) return rc;
   int rows = step_rows(&h);
@@ -1247,7 +1257,6 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
     return fail(LBF_E_ARG, "unknown launch %d", what);
   }
   if (a.slab) rows = lbf::kSlabRows;
-  *out = lbfast_launch_info{};
   out->one_plane = a.slab;
   out->lane_sites = a.lane_sites;
   out->tile_rows = rows;

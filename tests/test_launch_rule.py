@@ -49,3 +49,24 @@ def test_what_cannot_be_launched_is_refused():
     assert rc(_lib.LBF_LAUNCH_ADJOINT, lattice="27h") == _lib.LBF_E_UNSUPPORTED
     assert lib.lbfast_default_launch(None, 0, None, 0, ctypes.byref(out)) == _lib.LBF_E_ARG
     assert lib.lbfast_set_form(None, 1) == _lib.LBF_E_ARG
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s", "bf16s", "f16su"])
+@pytest.mark.parametrize("what", [_lib.LBF_LAUNCH_SET_F64, _lib.LBF_LAUNCH_SET_F32,
+                                  _lib.LBF_LAUNCH_GET_F64, _lib.LBF_LAUNCH_GET_F32])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 5, 7), (512, 512, 512), (1000, 1000, 858),
+                                   (1000, 1000, 859),
+                                   (1024, 1024, 1024), (1201, 1200, 1200), (1580, 1590, 1590)])
+def test_whole_state_conversions_stay_within_the_launch_limit(storage, what, shape):
+    """HIP takes fewer than 2^32 work-items per launch; larger states go plane
+    by plane.  Every launch covers its state."""
+    got = default_launch(shape, 19, storage, what=what)
+    n = shape[0] * shape[1] * shape[2]
+    assert got["blocks"] * got["block_threads"] < 2 ** 32
+    wide = storage == "f64" if what <= _lib.LBF_LAUNCH_SET_F32 else what == _lib.LBF_LAUNCH_GET_F64
+    per = (2 if wide else 4) if storage in ("f64", "f32") else (1 if n % 2 else 2)
+    items = 10 * n if storage in ("f64", "f32") else n
+    if got["blocks"]:
+        assert got["blocks"] * got["block_threads"] * per >= items
+    else:
+        assert items / per > 2 ** 32 - 512
