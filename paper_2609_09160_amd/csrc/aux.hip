@@ -203,16 +203,25 @@ __global__ void decode_kernel(const typename Storage<ST>::T* __restrict__ buf, U
 // per lane on the side that is written (512^3 FP32 2.20 ms -> 1.72, 6.2 TB/s;
 // FP32 to doubles with 32 bytes per lane lost a quarter to stores of half
 // lines).
+// V values in a row, aligned as a lane finds them: to their own size (8 bytes
+// for two floats), at most to the 16 bytes that the arrays are aligned to.
+template <typename T, int V>
+struct alignas(V * sizeof(T) < 16 ? V * sizeof(T) : 16) LaneValues {
+  T v[V];
+};
+static_assert(alignof(LaneValues<float, 2>) == 8 && alignof(LaneValues<double, 4>) == 16);
+
 template <typename From, typename To, bool NT>
 __global__ void __launch_bounds__(kThreads) convert_flat_kernel(const From* __restrict__ src,
                                                                 To* __restrict__ dst, int64_t n) {
   constexpr int V = 16 / sizeof(To);
-  using VF = From __attribute__((ext_vector_type(V), aligned(16)));
-  using VT = To __attribute__((ext_vector_type(V), aligned(16)));
+  using VT = To __attribute__((ext_vector_type(V)));
   const int64_t i = (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) * V;
   if (i + V <= n) {
-    const VF v = *reinterpret_cast<const VF*>(src + i);
-    const VT w = __builtin_convertvector(v, VT);
+    const LaneValues<From, V> a = *reinterpret_cast<const LaneValues<From, V>*>(src + i);
+    VT w;
+#pragma unroll
+    for (int k = 0; k < V; ++k) w[k] = static_cast<To>(a.v[k]);
     if constexpr (NT)
       __builtin_nontemporal_store(w, reinterpret_cast<VT*>(dst + i));
     else
