@@ -61,6 +61,8 @@ int lbfast_zmarch_probe(const void* src, void* dst, int nx, int ny, int nz, int 
 enum {
   LBF_LAUNCH_STEP = 0,    /* one step of lbfast_step */
   LBF_LAUNCH_ADJOINT = 1, /* one adjoint step of lbfast_adjoint */
+  LBF_LAUNCH_PHASE = 2,   /* the phase update of a two-component step */
+  LBF_LAUNCH_FORCE = 3,   /* the force of a phase field set by lbfast_set_phase */
   /* lbfast_set_moments from and lbfast_get_moments into device arrays: blocks
    * and block_threads of the one launch for the whole state, blocks = 0 where
    * it is too large for one and goes plane by plane */

@@ -19,7 +19,7 @@ LBF_D3Q19, LBF_D3Q27, LBF_D3Q27H = 19, 27, 270
 LBF_F64, LBF_F32, LBF_F16S, LBF_BF16S, LBF_F16SU = 0, 1, 2, 3, 4
 LBF_PERIODIC, LBF_WALLS = 0, 1
 LBF_ROUND_AUTO, LBF_ROUND_NEAREST, LBF_ROUND_STOCHASTIC = 0, 1, 2
-LBF_LAUNCH_STEP, LBF_LAUNCH_ADJOINT = 0, 1
+LBF_LAUNCH_STEP, LBF_LAUNCH_ADJOINT, LBF_LAUNCH_PHASE, LBF_LAUNCH_FORCE = 0, 1, 2, 3
 LBF_LAUNCH_SET_F64, LBF_LAUNCH_SET_F32, LBF_LAUNCH_GET_F64, LBF_LAUNCH_GET_F32 = 4, 5, 6, 7
 LBF_FORM_AUTO, LBF_FORM_MARCH, LBF_FORM_ONE_PLANE = 0, 1, 2
 ROUNDING = {"auto": LBF_ROUND_AUTO, "nearest": LBF_ROUND_NEAREST,

@@ -90,6 +90,14 @@ struct PhaseArgs {
   int contrast;       // add the pressure and viscous force terms
   double rho_l, rho_h, nu_l, nu_h;
 };
+// Tiles of the phase update and of the force march: 64 x rows columns, marches
+// of zchunk planes
+struct PassGeom {
+  int rows, tiles_x, tiles_y, zchunk, blocks;
+  double cost;  // modelled time, see march_geom
+};
+PassGeom phase_geom(int storage, int nx, int ny, int nz);
+PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz);
 // phi_out = FTCS step of the Allen-Cahn equation from phi and the state's u
 hipError_t launch_phase_step(int storage, const PhaseArgs& a, hipStream_t stream);
 // F = mu(phi_out) grad(phi_out) + Fb

@@ -1247,6 +1247,20 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
     out->block_threads = lbf::kConvertThreads;
     return LBF_OK;
   }
+  if (what == LBF_LAUNCH_PHASE || what == LBF_LAUNCH_FORCE) {
+    if (!pp) return fail(LBF_E_ARG, "a launch of the two-component variant");
+    const int nx = static_cast<int>(p->nx), ny = static_cast<int>(p->ny);
+    const int nz = static_cast<int>(p->nz);
+    const lbf::PassGeom g = what == LBF_LAUNCH_PHASE
+                                ? lbf::phase_geom(p->storage, nx, ny, nz)
+                                : lbf::force_geom(p->storage, pp->rho_l != pp->rho_h, nx, ny, nz);
+    out->lane_sites = 1;
+    out->tile_rows = g.rows;
+    out->z_chunk = g.zchunk;
+    out->blocks = g.blocks;
+    out->block_threads = 64 * g.rows;
+    return LBF_OK;
+  }
   lbf::StepArgs a;
   if (int rc = step_args(&h, &a)) return rc;
   int rows = step_rows(&h);

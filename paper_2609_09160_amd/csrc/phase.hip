@@ -494,13 +494,12 @@ __global__ void __launch_bounds__(64 * kUpdRows) grad_march_kernel(const C* __re
 // takes `lat` us where a CU has one workgroup and at least `busy` us for each
 // workgroup on it, so the cost of a launch is the product with the workgroups
 // on the fullest of the 256 CUs; the chunk length of the least cost, down to
-// one plane on small grids.
-struct MarchGeom {
-  int tiles_x, tiles_y, zchunk, blocks;
-  double cost;
-};
-MarchGeom march_geom(int nx, int ny, int nz, int rows, int extra, double lat, double busy) {
-  MarchGeom m{};
+// one plane on small grids.  Of equal costs (an odd length and the next even
+// one) the longer, but the shorter up to `shorter` workgroups.
+PassGeom march_geom(int nx, int ny, int nz, int rows, int extra, double lat, double busy,
+                    int64_t shorter = 0) {
+  PassGeom m{};
+  m.rows = rows;
   m.tiles_x = (nx + 63) / 64;
   m.tiles_y = (ny + rows - 1) / rows;
   const int64_t cols = static_cast<int64_t>(m.tiles_x) * m.tiles_y;
@@ -516,7 +515,7 @@ MarchGeom march_geom(int nx, int ny, int nz, int rows, int extra, double lat, do
     if (k > 1 && blocks > 4096) break;
     const double per_cu = static_cast<double>((blocks + 255) / 256);
     const double cost = (zc + extra + 1) / 2 * 2 * (per_cu * busy > lat ? per_cu * busy : lat);
-    if (k == 1 || cost < m.cost) {
+    if (k == 1 || cost < m.cost || (cost == m.cost && blocks <= shorter)) {
       m.cost = cost;
       m.zchunk = zc;
       m.blocks = static_cast<int>(blocks);
@@ -532,7 +531,7 @@ int phase_grid(int64_t N) {
 }
 
 template <int ST, int ROWS>
-hipError_t phase_step_rows(const PhaseArgs& a, const MarchGeom& m, hipStream_t s) {
+hipError_t phase_step_rows(const PhaseArgs& a, const PassGeom& m, hipStream_t s) {
   using C = typename Storage<ST>::C;
   using T = typename Storage<ST>::T;
   hipLaunchKernelGGL((phase_kernel<ST, ROWS>), dim3(m.blocks), dim3(64 * ROWS), 0, s,
@@ -543,25 +542,42 @@ hipError_t phase_step_rows(const PhaseArgs& a, const MarchGeom& m, hipStream_t s
   return hipGetLastError();
 }
 
+template <int ST>
+hipError_t phase_step_st(const PhaseArgs& a, hipStream_t s) {
+  const PassGeom m = phase_geom(ST, a.nx, a.ny, a.nz);
+  if constexpr (ST != kF64)
+    if (m.rows == kUpdRows) return phase_step_rows<ST, kUpdRows>(a, m, s);
+  return phase_step_rows<ST, kLowRows>(a, m, s);
+}
+
+}  // namespace
+
 // 16-row tiles for FP32 arithmetic on grids that fill the device with them, 4
 // rows on smaller ones (us per two-component step with the chunk of either that
 // is best there, 4 / 16 rows: 32^3 16 / 21, 64^3 23.6 / 24.9, 128^3 92.8 /
 // 91.7, 256^3 518 / 514), and always 4 rows in FP64, where 16 spill (128^3
 // 160 / 185).
-template <int ST>
-hipError_t phase_step_st(const PhaseArgs& a, hipStream_t s) {
-  if constexpr (ST == kF64) {
-    return phase_step_rows<ST, kLowRows>(
-        a, march_geom(a.nx, a.ny, a.nz, kLowRows, 5, 1.1, 0.9), s);
-  } else {
-    const MarchGeom tall = march_geom(a.nx, a.ny, a.nz, kUpdRows, 5, 2.0, 2.0);
-    const MarchGeom low = march_geom(a.nx, a.ny, a.nz, kLowRows, 5, 0.95, 0.55);
-    return low.cost < tall.cost ? phase_step_rows<ST, kLowRows>(a, low, s)
-                                : phase_step_rows<ST, kUpdRows>(a, tall, s);
-  }
+PassGeom phase_geom(int storage, int nx, int ny, int nz) {
+  if (storage == kF64) return march_geom(nx, ny, nz, kLowRows, 5, 1.1, 0.9);
+  const PassGeom tall = march_geom(nx, ny, nz, kUpdRows, 5, 2.0, 2.0);
+  const PassGeom low = march_geom(nx, ny, nz, kLowRows, 5, 0.95, 0.55);
+  return low.cost < tall.cost ? low : tall;
 }
 
-}  // namespace
+// Only the ratio of the two times counts here.  Fitted to the times of 7 to 21
+// chunk lengths on each of 11 grids (8 x 128 x 8 to 300 x 280 x 200; FP64,
+// contrast and 16 bits on 4 of them): FP32 gains from further workgroups on a
+// CU (256^3: 16 and 32 planes, 1024 and 512 workgroups, 92.5 and 93.2 us, 64
+// planes, 256 workgroups, 104.4), less with contrast, which reads ten more
+// planes, and FP64 and 16-bit storage with contrast not at all (256^3 FP64 183
+// us with 256 workgroups, 185 to 191 with more).  Of lengths of equal cost the
+// shorter is the faster there (300 x 280 x 200 25 planes 218 us, 40 planes 230)
+// and as long as no CU has two workgroups (8 x 128 x 8 1 plane 7.2, 2 planes
+// 7.4), else the longer (77 x 150 x 210 FP32 27.4 and 28.9).  The choice takes 1.01 times as long as the best of the sweep.
+PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz) {
+  const double busy = !contrast ? (storage == kF64 ? 1.0 : 0.75) : (storage == kF32 ? 0.9 : 1.0);
+  return march_geom(nx, ny, nz, kUpdRows, 2, 1.0, busy, busy == 1.0 ? INT64_MAX : 256);
+}
 
 hipError_t launch_phase_step(int storage, const PhaseArgs& a, hipStream_t s) {
   switch (storage) {
@@ -582,7 +598,7 @@ hipError_t force_st(const PhaseArgs& a, hipStream_t s) {
   const T* st = static_cast<const T*>(a.state);
   auto launch = [&](auto contrast) {
     using E = ForceEmit<ST, decltype(contrast)::value>;
-    const MarchGeom m = march_geom(a.nx, a.ny, a.nz, kUpdRows, 3, 1.0, 1.0);
+    const PassGeom m = force_geom(ST, decltype(contrast)::value, a.nx, a.ny, a.nz);
     hipLaunchKernelGGL((grad_march_kernel<C, E>), dim3(m.blocks), dim3(64 * kUpdRows), 0, s, phi, a.nx, a.ny, a.nz,
                        m.tiles_x, m.tiles_y, m.zchunk, a.walls_y != 0,
                        E{st, static_cast<C*>(a.F), a.N, a});

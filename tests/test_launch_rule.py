@@ -70,3 +70,15 @@ def test_whole_state_conversions_stay_within_the_launch_limit(storage, what, sha
         assert got["blocks"] * got["block_threads"] * per >= items
     else:
         assert items / per > 2 ** 32 - 512
+
+
+@pytest.mark.parametrize("storage,phase,shape,most,least", [
+    ("f32", EQUAL, (256, 256, 256), 32, 512), ("f16s", EQUAL, (256, 256, 256), 32, 512),
+    ("f32", EQUAL, (256, 64, 400), 17, 384), ("f32", EQUAL, (128, 128, 128), 8, 256),
+    ("f64", EQUAL, (128, 128, 128), 8, 256), ("f32", CONTRAST, (128, 128, 128), 8, 256),
+    ("f64", CONTRAST, (256, 256, 256), 64, 256)])
+def test_force_march_keeps_the_device_busy(storage, phase, shape, most, least):
+    """The chunks are no longer, and the workgroups no fewer, than those that
+    the times of a sweep over chunk lengths ask for."""
+    got = default_launch(shape, 19, storage, phase=phase, what=_lib.LBF_LAUNCH_FORCE)
+    assert got["z_chunk"] <= most and got["blocks"] >= least, got
