@@ -185,7 +185,9 @@ struct MarchForm {
   bool stencil;          // one more LDS slot (two-component step)
   double read, write;    // bytes per site
   int streams;           // separate arrays read at an x-halo site
+  bool cached_forms;     // there are kernels with plain stores (step_cached)
   double l0, l1, busy;   // us per plane, see march_us
+  double slab, slab_mem; // one-plane form, see slab_us
 };
 
 // Both state buffers within the 256 MB last-level cache, with room for the
@@ -260,6 +262,9 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
   if (h->Ffield || h->two_phase) f.read += 3 * c, f.streams += 3;
   if (h->two_phase) f.read += c, f.write += 3 * c, f.streams += 1;
   if (adjoint) f.read = 22 * c, f.write = 13 * c, f.streams = 13, f.stencil = false;
+  f.cached_forms = !adjoint;
+  f.slab = adjoint ? (c == 8 ? 12.0 : 10.0) : f.stencil ? 17.5 : h->Ffield ? 16.0 : 13.0;
+  f.slab_mem = adjoint ? 80 * c : 0.0;
   // fitted to the times of 250 to 900 launch shapes on each of 67 grids (8 x
   // 29 x 168 to 512^3), per velocity set and compute type
   const bool f64 = f.storage == LBF_F64;
@@ -271,8 +276,8 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
     f.l0 = f64 ? 1.3 : 1.15, f.l1 = f64 ? 0.2 : 0.045, f.busy = f64 ? 0.37 : 0.175;
   }
   // the stencils of the two-component step, and the adjoint's 22 values per
-  // site, by the same measure
-  const double heavier = h->two_phase ? 1.25 : (adjoint ? 1.5 : 1.0);
+  // site (see slab_us), by the same measure
+  const double heavier = h->two_phase ? 1.25 : (adjoint ? 1.65 : 1.0);
   f.l0 *= heavier, f.l1 *= heavier, f.busy *= heavier;
   return f;
 }
@@ -330,7 +335,7 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   const int64_t nx = h->p.nx, ny = h->p.ny, nz = h->p.nz;
   const int64_t cols = ceil_div(nx, 64 * S) * ceil_div(ny, ty);
   const bool fits = fits_cache(h);
-  const bool cached = step_cached(h, S, ty);
+  const bool cached = f.cached_forms && step_cached(h, S, ty);
   int64_t best = nz;
   double t_best = 0.0;
   bool have = false;
@@ -382,13 +387,21 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
 // after the other, 13 busy us each (16 with a force field, 17.5 with the stencils
 // of the two-component step), and no chain of planes before the first of them.
 // Fitted to both forms' times on 7 grids from 32^3 to 40 x 180 x 100 for each of
-// 15 forms: the choice takes 1.007 times as long as the better of the two in the
+// 12 forms: the choice takes 1.007 times as long as the better of the two in the
 // geometric mean, and no form has a march of those grids replaced by a one-plane
-// step that takes more than 1.13 times as long.
+// step that takes more than 1.13 times as long.  The adjoint step, 10 busy us
+// (FP64 12), is bound by memory on the larger grids: some 80 values per site (22
+// of the own plane, 13 of each neighbour, half as many again in the halo rows, 13
+// written).  Its constants are fitted to 975 grids and forms of 10 to 245 sites
+// a side, the one-plane form and a sweep of marches on each: rows, chunk and form
+// together take 1.013 times as long as the best of them (1.056 with the states'
+// stores left out of the march's time).
 double slab_us(const lbfast_ctx* h, const MarchForm& f) {
   const double w = static_cast<double>(ceil_div(h->p.nx, 64) * ceil_div(h->p.ny, lbf::kSlabRows)) *
                    static_cast<double>(h->p.nz);
-  return (f.stencil ? 17.5 : h->Ffield ? 16.0 : 13.0) * f.busy * std::ceil(w / 256.0) - 1.0;
+  const double issue = f.slab * f.busy * std::ceil(w / 256.0) - 1.0;
+  const double mem = f.slab_mem * static_cast<double>(h->N) / 9.0 * 1e-6;
+  return std::sqrt(issue * issue + mem * mem);
 }
 
 // the one-plane form in place of a march that is modelled to take `march` us

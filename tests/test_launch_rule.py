@@ -82,3 +82,17 @@ def test_force_march_keeps_the_device_busy(storage, phase, shape, most, least):
     the times of a sweep over chunk lengths ask for."""
     got = default_launch(shape, 19, storage, phase=phase, what=_lib.LBF_LAUNCH_FORCE)
     assert got["z_chunk"] <= most and got["blocks"] >= least, got
+
+
+@pytest.mark.parametrize("storage,Q,shape,rows", [("f64", 27, (64, 64, 64), 4),
+                                                  ("f32", 27, (16, 32, 72), 0),
+                                                  ("f32", 19, (16, 168, 24), 0),
+                                                  ("f32", 19, (128, 128, 128), 8),
+                                                  ("f64", 19, (96, 96, 96), 6)])
+def test_adjoint_shapes_in_the_cache(storage, Q, shape, rows):
+    """The adjoint step has no kernels with plain stores: shapes and forms are
+    compared with their stores counted (0: one plane per workgroup).  The one
+    that a sweep found to be the fastest, by 6% or more."""
+    got = default_launch(shape, Q, storage, field=True, what=_lib.LBF_LAUNCH_ADJOINT)
+    assert got["plain_stores"] == got["one_plane"]
+    assert (0 if got["one_plane"] else got["tile_rows"]) == rows
