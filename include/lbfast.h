@@ -256,15 +256,19 @@ int lbfast_set_launch(lbfast_t h, int tile_rows, int z_chunk);
  * results may differ between settings in the last bits. */
 int lbfast_set_lane_sites(lbfast_t h, int sites);
 
-/* Order in which the workgroups of the marching kernels (step, checkpointed
- * forward pass, adjoint) are handed to the GPU's 8 XCDs (each with its own
- * L2), for the calls that follow: 0 = automatic (contiguous
- * tile ranges per XCD for states that fit the last-level cache but the
- * smallest, for larger F64 ones with LBF_D3Q19 (the step) or more than 256
- * tile columns, the hardware's order otherwise),
+/* Order in which the workgroups of the steps and adjoint steps are handed to
+ * the GPU's 8 XCDs (each with its own L2), for the calls that follow:
+ * 0 = automatic.  Marches take contiguous tile ranges per XCD for states of 11
+ *     (16-bit storage: 24) to 120 MB, which the last-level cache keeps, and for
+ *     larger F64 ones with LBF_D3Q19 (the step) or more than 256 tile columns
+ *     (not with variable density or viscosity), else the hardware's order; 16-bit storage whose words depend on the
+ *     tiles (LBF_BF16S, LBF_D3Q27H, two components, LBF_F16SU with a force
+ *     field) always the hardware's order.  The one-plane kernel of small grids
+ *     takes contiguous ranges from 257 workgroups on.
  * 1 = the hardware's order (consecutive workgroups on the XCDs in turn),
- * 2 = a contiguous range of tiles per XCD.  A launch choice only: every
- * order computes bitwise the same results.  LBF_E_ARG for other values. */
+ * 2 = a contiguous range of tiles per XCD.
+ * A launch choice only: every order computes bitwise the same results.
+ * LBF_E_ARG for other values. */
 int lbfast_set_block_order(lbfast_t h, int order);
 
 /* Two-component variant (section 2): a phase field phi in [0, 1] (1: heavy

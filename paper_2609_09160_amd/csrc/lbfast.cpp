@@ -610,12 +610,19 @@ int adjoint_rows(const lbfast_ctx* h, const MarchForm& f, int sites) {
 // more columns than CUs (512^3 D3Q19 3.91 ms against 5.55; with fewer columns
 // D3Q27 and D3Q27h are as fast in either on 13 grids, but 320^3 1313 us against
 // 1115).  Elsewhere the hardware's order: marches of one wave of workgroups keep
-// step by themselves, and several waves lose about 10% in the other.
+// step by themselves, and several waves lose about 10% in the other.  The
+// two-component step is no exception: on 50 grids and forms in the cache the
+// contiguous order takes 0.94 times as long in the geometric mean (180 x 90 x 60
+// FP32 51.8 us per step of both passes against 75, 201 x 97 x 113 125 against
+// 145; at most 1.2% slower), and for FP64 D3Q19 beyond it 0.97 (128^3 140 and 153,
+// 256^3 969 and 1001), but not with contrast there (equal on six grids, 256 x 300
+// x 180 976 and 877).
 bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y, bool adjoint = false) {
   if (h->block_order != 0) return h->block_order == 2;
   // measured 6% slower for 16-bit D3Q27h at 267 x 122 x 127
-  if (h->two_phase || keeps_rows(h)) return false;
+  if (keeps_rows(h)) return false;
   if (fits_cache(h)) return cache_matters(h);
+  if (h->two_phase && variable_properties(h)) return false;
   return h->p.storage == LBF_F64 && ((h->p.lattice == LBF_D3Q19 && !adjoint) ||
                                      static_cast<int64_t>(tiles_x) * tiles_y > 256);
 }

@@ -96,3 +96,17 @@ def test_adjoint_shapes_in_the_cache(storage, Q, shape, rows):
     got = default_launch(shape, Q, storage, field=True, what=_lib.LBF_LAUNCH_ADJOINT)
     assert got["plain_stores"] == got["one_plane"]
     assert (0 if got["one_plane"] else got["tile_rows"]) == rows
+
+
+@pytest.mark.parametrize("storage,Q,shape,equal,contrast", [
+    ("f32", 19, (201, 97, 113), 1, 1), ("f32", 27, (180, 90, 60), 1, 1),
+    ("f64", 19, (100, 100, 100), 1, 1), ("f64", 27, (64, 200, 100), 1, 1),
+    ("f64", 19, (128, 128, 128), 1, 0), ("f64", 19, (256, 256, 256), 1, 0),
+    ("f64", 27, (512, 256, 100), 1, 0), ("f32", 27, (256, 256, 256), 0, 0),
+    ("f64", 27, (256, 256, 256), 0, 0), ("f16s", 19, (112, 112, 112), 0, 0)])
+def test_block_order_of_the_two_component_step(storage, Q, shape, equal, contrast):
+    """Contiguous where the state is in the last-level cache, and for FP64 with
+    equal properties and D3Q19 or many columns beyond it; 16-bit storage keeps
+    the hardware's order."""
+    assert default_launch(shape, Q, storage, phase=EQUAL)["contiguous"] == equal
+    assert default_launch(shape, Q, storage, phase=CONTRAST)["contiguous"] == contrast
