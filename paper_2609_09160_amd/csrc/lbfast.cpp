@@ -223,15 +223,6 @@ bool keeps_rows(const lbfast_ctx* h) {
   return keeps_parity(h) &&
          !(h->p.storage == LBF_F16SU && h->p.lattice != LBF_D3Q27H && !h->Ffield);
 }
-// FP16SU with D3Q19 and D3Q27 and a uniform force is contracted differently per
-// tile height, too, which shows in some low words of the velocity (27 of 100
-// drawn grids after 6 steps, up to 8e-4 of a state), but 8-row tiles give the
-// same words in every chunk of the kept parity, with plain stores and without.
-bool keeps_height(const lbfast_ctx* h) {
-  const bool uniform = !h->Ffield && (h->p.force[0] != 0.0 || h->p.force[1] != 0.0 ||
-                                      h->p.force[2] != 0.0);
-  return h->p.storage == LBF_F16SU && h->p.lattice != LBF_D3Q27H && uniform;
-}
 
 // States of at least a few MB gain from what the cache keeps (plain stores,
 // contiguous tile ranges per XCD); smaller ones lose a little (64^3 FP32, 10.5
@@ -495,7 +486,6 @@ void model_launch(lbfast_ctx* h) {
     if (is_16bit(h->p.storage) && !one_only && S != (two ? 2 : 1)) continue;
     for (int ty : lbf::kTileRowsSupported) {
       if (!shape_built(h, S, ty)) continue;
-      if (keeps_height(h) && ty != h->tile_rows) continue;
       if (ty > 6 && (S == 3 || (h->two_phase && h->p.lattice != LBF_D3Q19 && (S == 2 || f64)) ||
                      (f64 && h->p.lattice == LBF_D3Q27H && h->Ffield)))
         continue;
