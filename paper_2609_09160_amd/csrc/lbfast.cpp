@@ -254,8 +254,14 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
   if (h->two_phase) f.read += c, f.write += 3 * c, f.streams += 1;
   if (adjoint) f.read = 22 * c, f.write = 13 * c, f.streams = 13, f.stencil = false;
   f.cached_forms = !adjoint;
-  f.slab = adjoint ? (c == 8 ? 12.0 : 10.0) : f.stencil ? 17.5 : h->Ffield ? 16.0 : 13.0;
-  f.slab_mem = adjoint ? 80 * c : 0.0;
+  const bool c64 = c == 8.0, q19 = f.Q == LBF_D3Q19, full = f.Q == LBF_D3Q27H;
+  f.slab = q19 ? (c64 ? 12.0 : 11.5) : full ? (c64 ? 15.0 : 13.5) : (c64 ? 12.0 : 10.0);
+  if (f.stencil)
+    f.slab += full ? 0.5 : c64 ? 3.0 : 2.5;
+  else if (h->Ffield && q19)
+    f.slab += c64 ? 2.0 : 1.0;
+  f.slab_mem = c * ((f.stencil ? 70 : h->Ffield ? 50 : 30) + (full ? 20 : 0));
+  if (adjoint) f.slab = c64 ? 12.0 : 10.0, f.slab_mem = 80 * c;
   // fitted to the times of 250 to 900 launch shapes on each of 67 grids (8 x
   // 29 x 168 to 512^3), per velocity set and compute type
   const bool f64 = f.storage == LBF_F64;
@@ -375,18 +381,16 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
 }
 
 // Modelled time of the one-plane form, in march_us's terms: a CU's workgroups one
-// after the other, 13 busy us each (16 with a force field, 17.5 with the stencils
-// of the two-component step), and no chain of planes before the first of them.
-// Fitted to both forms' times on 7 grids from 32^3 to 40 x 180 x 100 for each of
-// 12 forms: the choice takes 1.007 times as long as the better of the two in the
-// geometric mean, and no form has a march of those grids replaced by a one-plane
-// step that takes more than 1.13 times as long.  The adjoint step, 10 busy us
-// (FP64 12), is bound by memory on the larger grids: some 80 values per site (22
-// of the own plane, 13 of each neighbour, half as many again in the halo rows, 13
-// written).  Its constants are fitted to 975 grids and forms of 10 to 245 sites
-// a side, the one-plane form and a sweep of marches on each: rows, chunk and form
-// together take 1.013 times as long as the best of them (1.056 with the states'
-// stores left out of the march's time).
+// after the other, `slab` busy us each, and no chain of planes before the first
+// of them, against what they read (the own plane and its two neighbours, half as
+// much again in the halo rows) and write, `slab_mem` bytes per site.  The step's
+// constants are fitted to both forms' times on 5448 grids and forms of 10 to 300
+// sites a side, states up to 120 MB: the choice takes 1.003 times as long as the
+// better of the two in the geometric mean (without the memory 1.010, and 176 x
+// 256 x 8 FP64 with a field 36.4 us instead of 24.4).  The adjoint's to 975 grids
+// and forms, the one-plane form and a sweep of marches on each: rows, chunk and
+// form together take 1.013 times as long as the best of them (1.056 with the
+// states' stores left out of the march's time).
 double slab_us(const lbfast_ctx* h, const MarchForm& f) {
   const double w = static_cast<double>(ceil_div(h->p.nx, 64) * ceil_div(h->p.ny, lbf::kSlabRows)) *
                    static_cast<double>(h->p.nz);

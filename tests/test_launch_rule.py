@@ -110,3 +110,15 @@ def test_block_order_of_the_two_component_step(storage, Q, shape, equal, contras
     the hardware's order."""
     assert default_launch(shape, Q, storage, phase=EQUAL)["contiguous"] == equal
     assert default_launch(shape, Q, storage, phase=CONTRAST)["contiguous"] == contrast
+
+
+@pytest.mark.parametrize("storage,Q,shape,kind,one_plane", [
+    ("f64", 19, (176, 256, 8), {"field": True}, 0), ("f32", 19, (192, 232, 24), {"field": True}, 0),
+    ("f32", 19, (61, 253, 170), {"phase": CONTRAST}, 0),
+    ("f32", 19, (224, 184, 32), {"phase": CONTRAST}, 0), ("f32", 19, (248, 232, 16), {}, 0),
+    ("f32", 27, (16, 72, 48), {"field": True}, 1), ("f32", 27, (16, 56, 104), {}, 1),
+    ("f32", 19, (8, 56, 112), {"field": True}, 1), ("f32", 27, (16, 24, 296), {}, 1)])
+def test_one_plane_form_against_its_memory_time(storage, Q, shape, kind, one_plane):
+    """The form that both forms' times name, by 15% or more: the one-plane form
+    reads three planes for one, which decides on larger grids."""
+    assert default_launch(shape, Q, storage, **kind)["one_plane"] == one_plane
