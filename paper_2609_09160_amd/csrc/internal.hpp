@@ -98,8 +98,10 @@ struct PassGeom {
 };
 PassGeom phase_geom(int storage, int nx, int ny, int nz);
 PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz);
-// phi_out = FTCS step of the Allen-Cahn equation from phi and the state's u
-hipError_t launch_phase_step(int storage, const PhaseArgs& a, hipStream_t stream);
+// phi_out = FTCS step of the Allen-Cahn equation from phi and the state's u, in
+// the tiles of phase_geom
+hipError_t launch_phase_step(int storage, const PhaseArgs& a, const PassGeom& m,
+                             hipStream_t stream);
 // F = mu(phi_out) grad(phi_out) + Fb
 hipError_t launch_capillary_force(int storage, const PhaseArgs& a, hipStream_t stream);
 // n values between a user array (F64 or F32) and the compute type of the storage:

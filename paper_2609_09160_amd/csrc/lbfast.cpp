@@ -132,6 +132,13 @@ int validate(const lbfast_params* p) {
 
 }  // namespace
 
+// Launch geometry of a step or an adjoint step
+struct Launch {
+  int slab, cached, xcd_remap;       // as in lbf::StepArgs
+  int lane_sites, rows;
+  int tiles_x, tiles_y, zchunk, zchunks;
+};
+
 struct lbfast_ctx {
   lbfast_params p;
   int device = 0;
@@ -161,6 +168,10 @@ struct lbfast_ctx {
   int adj_sites = 0, adj_rows = 0;  // adjoint launch shape (0: automatic)
   int block_order = 0;              // 0 automatic, 1 hardware order, 2 per-XCD ranges
   int form = LBF_FORM_AUTO;         // march or one-plane form of the steps
+  // What the settings above come to, kept so that a call of few steps does not
+  // evaluate the launch model: see plan()
+  Launch step;
+  lbf::PassGeom phase;              // two-component variant
 };
 
 namespace {
@@ -509,73 +520,45 @@ void model_launch(lbfast_ctx* h) {
   h->auto_slab = !is_16bit(h->p.storage) && slab_pays(h, f, t_best);
 }
 
-// problem and default launch shapes of a new handle
-void set_params(lbfast_ctx* h, const lbfast_params* p) {
-  h->p = *p;
-  h->N = p->nx * p->ny * p->nz;
-  width_launch(h);
-  model_launch(h);
-}
-
-// The shapes of a handle that has become a two-component one.
-void two_phase_launch(lbfast_ctx* h) {
-  // A shape chosen by the caller is kept where it can be.  The two-component
-  // step has one- and two-site forms of at most 8 rows,
-  // with one more LDS slot (phi(t+1)) than the one-component step.  With
-  // variable density or viscosity, one site per lane: the two-site form
-  // spills registers there (measured at 256^3 FP32: 0.80 ms against 0.57).
-  const bool one_site = h->lane_sites == 3 || (h->lane_sites == 2 && variable_properties(h));
-  const bool reshape = one_site || h->tile_rows > 8 ||
-                       lds_bytes(h->p.lattice, h->p.storage, h->tile_rows, h->lane_sites,
-                                 true) > kLdsLimit;
-  if (one_site) h->lane_sites = 1;
-  if (reshape) {
-    h->tile_rows = 4;
-    for (int ty : {8, 6})
-      if (lds_bytes(h->p.lattice, h->p.storage, ty, h->lane_sites, true) <= kLdsLimit) {
-        h->tile_rows = ty;
-        break;
-      }
-  }
-  model_launch(h);
-}
-
 bool step_slab(const lbfast_ctx* h) {
   if (h->form != LBF_FORM_AUTO) return h->form == LBF_FORM_ONE_PLANE;
   return !h->shape_set && h->z_chunk == 0 && h->auto_slab;
 }
 
 // launch geometry of the one-plane form
-void slab_args(const lbfast_ctx* h, lbf::StepArgs* a) {
-  a->slab = 1;
-  a->cached = 0;
-  a->lane_sites = 1;
-  a->tiles_x = static_cast<int>(ceil_div(h->p.nx, 64));
-  a->tiles_y = static_cast<int>(ceil_div(h->p.ny, lbf::kSlabRows));
-  a->zchunk = 1;
-  a->zchunks = static_cast<int>(h->p.nz);
+Launch slab_launch(const lbfast_ctx* h) {
+  Launch l{};
+  l.slab = 1;
+  l.lane_sites = 1;
+  l.rows = lbf::kSlabRows;
+  l.tiles_x = static_cast<int>(ceil_div(h->p.nx, 64));
+  l.tiles_y = static_cast<int>(ceil_div(h->p.ny, lbf::kSlabRows));
+  l.zchunk = 1;
+  l.zchunks = static_cast<int>(h->p.nz);
   // z-neighbours on one XCD once a CU has more than one workgroup (48^3 FP32
   // 5.7 us, 7.7 in the hardware's order; 32^3 4.1 and 3.8)
-  a->xcd_remap = h->block_order != 0
-                     ? h->block_order == 2
-                     : static_cast<int64_t>(a->tiles_x) * a->tiles_y * h->p.nz > 256;
+  l.xcd_remap = h->block_order != 0
+                    ? h->block_order == 2
+                    : static_cast<int64_t>(l.tiles_x) * l.tiles_y * h->p.nz > 256;
+  return l;
 }
 
 int step_sites(const lbfast_ctx* h) { return h->shape_set ? h->lane_sites : h->auto_sites; }
 int step_rows(const lbfast_ctx* h) { return h->shape_set ? h->tile_rows : h->auto_rows; }
 
-int resolve_zchunk(const lbfast_ctx* h, const MarchForm& f, int lane_sites, int tile_rows,
-                   int* tiles_x, int* tiles_y, int* zchunks, int* zchunk) {
-  *tiles_x = static_cast<int>(ceil_div(h->p.nx, 64 * lane_sites));
-  *tiles_y = static_cast<int>(ceil_div(h->p.ny, tile_rows));
-  const int64_t cols = static_cast<int64_t>(*tiles_x) * *tiles_y;
+// tiles and z-chunks of a march of the given shape
+Launch march_launch(const lbfast_ctx* h, const MarchForm& f, int lane_sites, int rows) {
+  Launch l{};
+  l.lane_sites = lane_sites;
+  l.rows = rows;
+  l.tiles_x = static_cast<int>(ceil_div(h->p.nx, 64 * lane_sites));
+  l.tiles_y = static_cast<int>(ceil_div(h->p.ny, rows));
   int64_t zc = h->z_chunk;
-  if (zc <= 0) zc = best_zchunk(h, f, lane_sites, tile_rows, nullptr);
+  if (zc <= 0) zc = best_zchunk(h, f, lane_sites, rows, nullptr);
   if (zc > h->p.nz) zc = h->p.nz;
-  *zchunk = static_cast<int>(zc);
-  *zchunks = static_cast<int>(ceil_div(h->p.nz, zc));
-  if (static_cast<int64_t>(*zchunks) * cols > 0x7fffffff) return fail(LBF_E_ARG, "grid too large");
-  return LBF_OK;
+  l.zchunk = static_cast<int>(zc);
+  l.zchunks = static_cast<int>(ceil_div(h->p.nz, zc));
+  return l;
 }
 
 // Rows per tile of the adjoint step: 8 (FP64: 6, taller tiles spill), or fewer
@@ -621,6 +604,55 @@ bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y, bool adjoin
                                      static_cast<int64_t>(tiles_x) * tiles_y > 256);
 }
 
+// The launches that the handle's settings come to; whatever changes one of them
+// (the set_ calls, the force field, the two-component variant) calls this.
+void plan(lbfast_ctx* h) {
+  if (step_slab(h)) {
+    h->step = slab_launch(h);
+  } else {
+    const int sites = step_sites(h), rows = step_rows(h);
+    h->step = march_launch(h, march_form(h), sites, rows);
+    h->step.cached = step_cached(h, sites, rows);
+    h->step.xcd_remap = contiguous_order(h, h->step.tiles_x, h->step.tiles_y);
+  }
+  if (h->two_phase)
+    h->phase = lbf::phase_geom(h->p.storage, static_cast<int>(h->p.nx),
+                               static_cast<int>(h->p.ny), static_cast<int>(h->p.nz));
+}
+
+// problem and default launch shapes of a new handle
+void set_params(lbfast_ctx* h, const lbfast_params* p) {
+  h->p = *p;
+  h->N = p->nx * p->ny * p->nz;
+  width_launch(h);
+  model_launch(h);
+  plan(h);
+}
+
+// The shapes of a handle that has become a two-component one.
+void two_phase_launch(lbfast_ctx* h) {
+  // A shape chosen by the caller is kept where it can be.  The two-component
+  // step has one- and two-site forms of at most 8 rows,
+  // with one more LDS slot (phi(t+1)) than the one-component step.  With
+  // variable density or viscosity, one site per lane: the two-site form
+  // spills registers there (measured at 256^3 FP32: 0.80 ms against 0.57).
+  const bool one_site = h->lane_sites == 3 || (h->lane_sites == 2 && variable_properties(h));
+  const bool reshape = one_site || h->tile_rows > 8 ||
+                       lds_bytes(h->p.lattice, h->p.storage, h->tile_rows, h->lane_sites,
+                                 true) > kLdsLimit;
+  if (one_site) h->lane_sites = 1;
+  if (reshape) {
+    h->tile_rows = 4;
+    for (int ty : {8, 6})
+      if (lds_bytes(h->p.lattice, h->p.storage, ty, h->lane_sites, true) <= kLdsLimit) {
+        h->tile_rows = ty;
+        break;
+      }
+  }
+  model_launch(h);
+  plan(h);
+}
+
 int check_handle(lbfast_t h) {
   if (!h) return fail(LBF_E_ARG, "handle is NULL");
   return LBF_OK;
@@ -653,6 +685,20 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   return a && b && x < y + nb && y < x + na;
 }
 
+int set_geometry(const Launch& l, lbf::StepArgs* a) {
+  if (static_cast<int64_t>(l.tiles_x) * l.tiles_y * l.zchunks > 0x7fffffff)
+    return fail(LBF_E_ARG, "grid too large");
+  a->slab = l.slab;
+  a->cached = l.cached;
+  a->xcd_remap = l.xcd_remap;
+  a->lane_sites = l.lane_sites;
+  a->tiles_x = l.tiles_x;
+  a->tiles_y = l.tiles_y;
+  a->zchunk = l.zchunk;
+  a->zchunks = l.zchunks;
+  return LBF_OK;
+}
+
 // launch geometry, relaxation, force and scales of the handle's step
 int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
   *a = lbf::StepArgs{};
@@ -660,13 +706,7 @@ int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
   a->ny = static_cast<int>(h->p.ny);
   a->nz = static_cast<int>(h->p.nz);
   a->N = h->N;
-  a->lane_sites = step_sites(h);
-  if (int rc = resolve_zchunk(h, march_form(h), a->lane_sites, step_rows(h), &a->tiles_x,
-                              &a->tiles_y, &a->zchunks, &a->zchunk))
-    return rc;
-  a->cached = step_cached(h, a->lane_sites, step_rows(h));
-  a->xcd_remap = contiguous_order(h, a->tiles_x, a->tiles_y);
-  if (step_slab(h)) slab_args(h, a);
+  if (int rc = set_geometry(h->step, a)) return rc;
   a->omega = 1.0 / h->p.tau;
   for (int k = 0; k < 3; ++k) a->F[k] = h->Ffield ? 0.0 : h->p.force[k];
   for (int k = 0; k < 10; ++k) {
@@ -700,24 +740,19 @@ int step_args(const lbfast_ctx* h, lbf::StepArgs* a) {
 // site: by default one site per lane and 8-row tiles (FP64: 6);
 // lbfast_set_adjoint_launch may choose two or three sites per lane with 4- or
 // 6-row tiles (FP32).
-int adjoint_launch(const lbfast_ctx* h, lbf::StepArgs* a, int* rows) {
+Launch adjoint_launch(const lbfast_ctx* h) {
+  if (h->form == LBF_FORM_ONE_PLANE) return slab_launch(h);
   const MarchForm f = march_form(h, true);
-  a->lane_sites = h->adj_sites ? h->adj_sites : 1;
-  *rows = adjoint_rows(h, f, a->lane_sites);
-  a->slab = 0;
-  a->cached = 0;
-  if (int rc = resolve_zchunk(h, f, a->lane_sites, *rows, &a->tiles_x, &a->tiles_y, &a->zchunks,
-                              &a->zchunk))
-    return rc;
-  a->xcd_remap = contiguous_order(h, a->tiles_x, a->tiles_y, true);
-  bool one_plane = h->form == LBF_FORM_ONE_PLANE;
+  const int sites = h->adj_sites ? h->adj_sites : 1;
+  const int rows = adjoint_rows(h, f, sites);
   if (h->form == LBF_FORM_AUTO && !h->adj_sites && !h->adj_rows && h->z_chunk == 0) {
     double march;
-    (void)best_zchunk(h, f, a->lane_sites, *rows, &march);
-    one_plane = slab_pays(h, f, march);
+    (void)best_zchunk(h, f, sites, rows, &march);
+    if (slab_pays(h, f, march)) return slab_launch(h);
   }
-  if (one_plane) slab_args(h, a);
-  return LBF_OK;
+  Launch l = march_launch(h, f, sites, rows);
+  l.xcd_remap = contiguous_order(h, l.tiles_x, l.tiles_y, true);
+  return l;
 }
 
 // seed of the stochastic rounding of step t (16-bit storage): the step
@@ -731,8 +766,7 @@ uint32_t step_seed(uint64_t t) {
 }
 
 int launch_forward(const lbfast_ctx* h, const lbf::StepArgs& a) {
-  hipError_t e = lbf::launch_step(h->p.lattice, h->p.storage,
-                                  a.slab ? lbf::kSlabRows : step_rows(h),
+  hipError_t e = lbf::launch_step(h->p.lattice, h->p.storage, h->step.rows,
                                   h->p.bc[1] == LBF_WALLS, a, h->stream);
   if (e != hipSuccess) return hip_fail(e, "step launch");
   return LBF_OK;
@@ -1081,7 +1115,10 @@ int lbfast_set_force_field(lbfast_t h, const void* F_dev, int dtype) {
   if (!F_dev) {
     const bool had = h->Ffield != nullptr;
     h->Ffield = nullptr;
-    if (had) model_launch(h);
+    if (had) {
+      model_launch(h);
+      plan(h);
+    }
     return LBF_OK;
   }
   const int want = (h->p.storage == LBF_F64) ? LBF_F64 : LBF_F32;
@@ -1093,7 +1130,10 @@ int lbfast_set_force_field(lbfast_t h, const void* F_dev, int dtype) {
   if (!is_device_ptr(F_dev)) return fail(LBF_E_ARG, "force field must be device memory");
   const bool had = h->Ffield != nullptr;
   h->Ffield = F_dev;
-  if (!had) model_launch(h);
+  if (!had) {
+    model_launch(h);
+    plan(h);
+  }
   return LBF_OK;
 }
 
@@ -1119,6 +1159,7 @@ int lbfast_set_launch(lbfast_t h, int tile_rows, int z_chunk) {
     h->shape_set = true;
   }
   if (z_chunk) h->z_chunk = z_chunk;
+  plan(h);
   return LBF_OK;
 }
 
@@ -1127,6 +1168,7 @@ int lbfast_set_block_order(lbfast_t h, int order) {
   if (int rc = check_handle(h)) return rc;
   if (order < 0 || order > 2) return fail(LBF_E_ARG, "order must be 0, 1 or 2");
   h->block_order = order;
+  plan(h);
   return LBF_OK;
 }
 
@@ -1156,6 +1198,7 @@ int lbfast_set_lane_sites(lbfast_t h, int sites) {
   h->lane_sites = sites;
   h->tile_rows = ty;
   h->shape_set = true;
+  plan(h);
   return LBF_OK;
 }
 
@@ -1198,7 +1241,7 @@ int lbfast_step(lbfast_t h, int64_t n) {
     if (h->two_phase) {
       // phi(t+1) first: the step computes F(t+1) from it for the correction
       lbf::PhaseArgs pa = phase_args(h);
-      hipError_t e = lbf::launch_phase_step(h->p.storage, pa, h->stream);
+      hipError_t e = lbf::launch_phase_step(h->p.storage, pa, h->phase, h->stream);
       if (e != hipSuccess) return hip_fail(e, "phase-field launch");
       a.Ffield = h->Fph[h->pcur];
       a.Fout = h->Fph[h->pcur ^ 1];
@@ -1228,6 +1271,7 @@ int lbfast_set_form(lbfast_t h, int form) {
       return fail(LBF_E_UNSUPPORTED, "the one-plane form is for small grids");
   }
   h->form = form;
+  plan(h);
   return LBF_OK;
 }
 
@@ -1247,6 +1291,7 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
   if (force_field) {
     h.Ffield = out;  // any address: only whether there is one counts here
     model_launch(&h);
+    plan(&h);
   }
   if (pp) {
     h.pp = *pp;
@@ -1263,11 +1308,11 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
   }
   if (what == LBF_LAUNCH_PHASE || what == LBF_LAUNCH_FORCE) {
     if (!pp) return fail(LBF_E_ARG, "a launch of the two-component variant");
-    const int nx = static_cast<int>(p->nx), ny = static_cast<int>(p->ny);
-    const int nz = static_cast<int>(p->nz);
-    const lbf::PassGeom g = what == LBF_LAUNCH_PHASE
-                                ? lbf::phase_geom(p->storage, nx, ny, nz)
-                                : lbf::force_geom(p->storage, pp->rho_l != pp->rho_h, nx, ny, nz);
+    const lbf::PassGeom g =
+        what == LBF_LAUNCH_PHASE
+            ? h.phase
+            : lbf::force_geom(p->storage, pp->rho_l != pp->rho_h, static_cast<int>(p->nx),
+                              static_cast<int>(p->ny), static_cast<int>(p->nz));
     out->lane_sites = 1;
     out->tile_rows = g.rows;
     out->z_chunk = g.zchunk;
@@ -1275,24 +1320,21 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
     out->block_threads = 64 * g.rows;
     return LBF_OK;
   }
-  lbf::StepArgs a;
-  if (int rc = step_args(&h, &a)) return rc;
-  int rows = step_rows(&h);
+  Launch l = h.step;
   if (what == LBF_LAUNCH_ADJOINT) {
     if (int rc = check_adjoint_args(&h, 1, 1)) return rc;
-    if (int rc = adjoint_launch(&h, &a, &rows)) return rc;
+    l = adjoint_launch(&h);
   } else if (what != LBF_LAUNCH_STEP) {
     return fail(LBF_E_ARG, "unknown launch %d", what);
   }
-  if (a.slab) rows = lbf::kSlabRows;
-  out->one_plane = a.slab;
-  out->lane_sites = a.lane_sites;
-  out->tile_rows = rows;
-  out->z_chunk = a.zchunk;
-  out->contiguous = a.xcd_remap;
-  out->plain_stores = a.slab || a.cached;
-  out->blocks = static_cast<int64_t>(a.tiles_x) * a.tiles_y * a.zchunks;
-  out->block_threads = 64 * (rows + 2);
+  out->one_plane = l.slab;
+  out->lane_sites = l.lane_sites;
+  out->tile_rows = l.rows;
+  out->z_chunk = l.zchunk;
+  out->contiguous = l.xcd_remap;
+  out->plain_stores = l.slab || l.cached;
+  out->blocks = static_cast<int64_t>(l.tiles_x) * l.tiles_y * l.zchunks;
+  out->block_threads = 64 * (l.rows + 2);
   return LBF_OK;
 }
 
@@ -1529,8 +1571,8 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
   if (int rc = step_args(h, &fa)) return rc;
   aa = fa;
   aa.gF = gF_dev;
-  int adj_rows = 0;
-  if (int rc = adjoint_launch(h, &aa, &adj_rows)) return rc;
+  const Launch adj = adjoint_launch(h);
+  if (int rc = set_geometry(adj, &aa)) return rc;
   const bool walls_y = h->p.bc[1] == LBF_WALLS;
   for (int64_t seg = nseg - 1; seg >= 0; --seg) {
     const int64_t len = std::min(every, nsteps - seg * every);
@@ -1555,7 +1597,7 @@ int lbfast_adjoint(lbfast_t h, int64_t nsteps, int64_t every, const void* ckpt_d
       if (l0_direct && seg == 0 && j == 0) aa.dst = lambda0_dev;
       aa.state_old = state(j);
       aa.state_new = state(j + 1);
-      e = lbf::launch_adjoint(h->p.lattice, h->p.storage, adj_rows, walls_y, aa, h->stream);
+      e = lbf::launch_adjoint(h->p.lattice, h->p.storage, adj.rows, walls_y, aa, h->stream);
       if (e != hipSuccess) return hip_fail(e, "adjoint launch");
       lam_src = aa.dst;
     }

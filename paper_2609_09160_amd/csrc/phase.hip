@@ -543,8 +543,7 @@ hipError_t phase_step_rows(const PhaseArgs& a, const PassGeom& m, hipStream_t s)
 }
 
 template <int ST>
-hipError_t phase_step_st(const PhaseArgs& a, hipStream_t s) {
-  const PassGeom m = phase_geom(ST, a.nx, a.ny, a.nz);
+hipError_t phase_step_st(const PhaseArgs& a, const PassGeom& m, hipStream_t s) {
   if constexpr (ST != kF64)
     if (m.rows == kUpdRows) return phase_step_rows<ST, kUpdRows>(a, m, s);
   return phase_step_rows<ST, kLowRows>(a, m, s);
@@ -579,12 +578,13 @@ PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz) {
   return march_geom(nx, ny, nz, kUpdRows, 2, 1.0, busy, busy == 1.0 ? INT64_MAX : 256);
 }
 
-hipError_t launch_phase_step(int storage, const PhaseArgs& a, hipStream_t s) {
+hipError_t launch_phase_step(int storage, const PhaseArgs& a, const PassGeom& m,
+                             hipStream_t s) {
   switch (storage) {
-    case kF64: return phase_step_st<kF64>(a, s);
-    case kF32: return phase_step_st<kF32>(a, s);
-    case kF16S: return phase_step_st<kF16S>(a, s);
-    case kBF16S: return phase_step_st<kBF16S>(a, s);
+    case kF64: return phase_step_st<kF64>(a, m, s);
+    case kF32: return phase_step_st<kF32>(a, m, s);
+    case kF16S: return phase_step_st<kF16S>(a, m, s);
+    case kBF16S: return phase_step_st<kBF16S>(a, m, s);
     default: return hipErrorInvalidValue;
   }
 }
