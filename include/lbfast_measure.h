@@ -56,6 +56,7 @@ int lbfast_zmarch_probe(const void* src, void* dst, int nx, int ny, int nz, int 
                         int zchunk, void* stream);
 
 /* What a new handle for `p` launches for one call, without a GPU:
+ * compute_units of the device (0: 256, an MI355X in one partition),
  * force_field != 0 with a per-site force field set, pp != NULL with the
  * two-component variant enabled (not both). */
 enum {
@@ -81,8 +82,8 @@ typedef struct lbfast_launch_info {
   int64_t blocks;       /* workgroups, and work-items of each */
   int64_t block_threads;
 } lbfast_launch_info;
-int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_phase_params* pp,
-                          int what, lbfast_launch_info* out);
+int lbfast_default_launch(const lbfast_params* p, int compute_units, int force_field,
+                          const lbfast_phase_params* pp, int what, lbfast_launch_info* out);
 
 /* The form of the steps and adjoint steps that follow: LBF_FORM_AUTO as the
  * library chooses, LBF_FORM_MARCH, or LBF_FORM_ONE_PLANE (F32 and F64 storage,

@@ -108,7 +108,7 @@ def load():
         "lbfast_adjoint": ([vp, i64, i64, vp, vp, vp, vp, vp], i32),
         "lbfast_set_adjoint_launch": ([vp, i32, i32], i32),
         "lbfast_set_form": ([vp, i32], i32),
-        "lbfast_default_launch": ([P, i32, ctypes.POINTER(LbfastPhaseParams), i32,
+        "lbfast_default_launch": ([P, i32, i32, ctypes.POINTER(LbfastPhaseParams), i32,
                                    ctypes.POINTER(LbfastLaunchInfo)], i32),
     }
     for name, (args, res) in sig.items():

@@ -96,14 +96,15 @@ struct PassGeom {
   int rows, tiles_x, tiles_y, zchunk, blocks;
   double cost;  // modelled time, see march_geom
 };
-PassGeom phase_geom(int storage, int nx, int ny, int nz);
-PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz);
+PassGeom phase_geom(int storage, int nx, int ny, int nz, int cus);
+PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz, int cus);
 // phi_out = FTCS step of the Allen-Cahn equation from phi and the state's u, in
 // the tiles of phase_geom
 hipError_t launch_phase_step(int storage, const PhaseArgs& a, const PassGeom& m,
                              hipStream_t stream);
-// F = mu(phi_out) grad(phi_out) + Fb
-hipError_t launch_capillary_force(int storage, const PhaseArgs& a, hipStream_t stream);
+// F = mu(phi_out) grad(phi_out) + Fb, in the tiles of force_geom
+hipError_t launch_capillary_force(int storage, const PhaseArgs& a, const PassGeom& m,
+                                  hipStream_t stream);
 // n values between a user array (F64 or F32) and the compute type of the storage:
 // dst_is_user = 0 converts user -> compute type, 1 compute type -> user
 hipError_t launch_convert(int storage, int user_dtype, const void* src, int dst_is_user,

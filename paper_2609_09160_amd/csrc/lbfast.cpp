@@ -171,7 +171,8 @@ struct lbfast_ctx {
   // What the settings above come to, kept so that a call of few steps does not
   // evaluate the launch model: see plan()
   Launch step;
-  lbf::PassGeom phase;              // two-component variant
+  lbf::PassGeom phase, force;       // two-component variant
+  int cus = 256;                    // compute units of the device
 };
 
 namespace {
@@ -194,6 +195,7 @@ constexpr size_t kLdsLimit = 160 * 1024;
 struct MarchForm {
   int Q, storage;
   bool stencil;          // one more LDS slot (two-component step)
+  int cus;               // compute units of the device
   double read, write;    // bytes per site
   int streams;           // separate arrays read at an x-halo site
   bool cached_forms;     // there are kernels with plain stores (step_cached)
@@ -257,6 +259,7 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
   f.Q = h->p.lattice;
   f.storage = h->p.storage;
   f.stencil = h->two_phase;
+  f.cus = h->cus;
   const double e = static_cast<double>(elem_bytes(f.storage));
   const double c = f.storage == LBF_F64 ? 8.0 : 4.0;
   f.read = f.write = static_cast<double>(state_planes(f.storage)) * e;
@@ -310,7 +313,7 @@ double march_us(const MarchForm& f, int64_t nx, int64_t ny, int64_t nz, bool fit
   const double N = static_cast<double>(nx) * static_cast<double>(ny) * static_cast<double>(nz);
   const double w = tx * tyn * nch;
   const double planes = 2.0 * static_cast<double>(ceil_div(zc + 2, 2));
-  const double per_cu = std::ceil(w / 256.0);
+  const double per_cu = std::ceil(w / f.cus);
   const double fit_lds =
       static_cast<double>(kLdsLimit / lds_bytes(f.Q, f.storage, ty, S, f.stencil));
   const double resident = std::min(per_cu, std::max(1.0, std::min(fit_lds, 32.0 / (ty + 2))));
@@ -323,7 +326,7 @@ double march_us(const MarchForm& f, int64_t nx, int64_t ny, int64_t nz, bool fit
                               2.0 * 2.0 * nch / static_cast<double>(nz)) +
                 1.6 * 2.0 * 128.0 * f.streams * tx * static_cast<double>(ny) *
                     static_cast<double>(nz);
-  if (!fits && w > 256.0 && tx * tyn <= 256.0) read *= 1.1;
+  if (!fits && w > f.cus && tx * tyn <= f.cus) read *= 1.1;
   const double mem = (read / 9.0 + (cached ? 0.0 : f.write * N / 5.6)) * 1e-6;
   return std::sqrt(issue * issue + mem * mem);
 }
@@ -363,12 +366,12 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   };
   if (fixed) {
     consider(by_width);
-  } else if (!fits && cols >= 256) {
+  } else if (!fits && cols >= f.cus) {
     // a column for every CU: about 512 workgroups in chunks of >= 64 planes
     // (512^3 FP32: 2.00 ms, one chunk per column 2.02), FP64 with two sites
     // per lane 1024 (3.91 ms, one chunk per column 4.35; D3Q27h with one site
     // and 8 rows 4.70 ms, one chunk per column 4.07)
-    const int64_t target = f.storage == LBF_F64 && S == 2 ? 1024 : 512;
+    const int64_t target = (f.storage == LBF_F64 && S == 2 ? 4 : 2) * int64_t{f.cus};
     const int64_t zc = ceil_div(nz, std::min(std::max<int64_t>(1, target / cols),
                                              std::max<int64_t>(1, nz / 64)));
     consider(even_only && zc < nz ? zc + zc % 2 : zc);
@@ -382,7 +385,7 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
         continue;
       }
       last = zc;
-      if (k > 1 && cols * k > 2048) break;
+      if (k > 1 && cols * k > 8 * int64_t{f.cus}) break;
       if (!even_only || zc % 2 == 0 || zc == nz) consider(zc);
       if (zc == 1) break;
     }
@@ -405,7 +408,7 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
 double slab_us(const lbfast_ctx* h, const MarchForm& f) {
   const double w = static_cast<double>(ceil_div(h->p.nx, 64) * ceil_div(h->p.ny, lbf::kSlabRows)) *
                    static_cast<double>(h->p.nz);
-  const double issue = f.slab * f.busy * std::ceil(w / 256.0) - 1.0;
+  const double issue = f.slab * f.busy * std::ceil(w / f.cus) - 1.0;
   const double mem = f.slab_mem * static_cast<double>(h->N) / 9.0 * 1e-6;
   return std::sqrt(issue * issue + mem * mem);
 }
@@ -484,7 +487,7 @@ void model_launch(lbfast_ctx* h) {
   const bool two = nx % 2 == 0 && nx >= 128 &&
                    ceil_div(nx, 128) * 128 - nx <= ceil_div(nx, 64) * 64 - nx;
   const bool wide27 = f64 && h->p.lattice == LBF_D3Q27 && two && !h->Ffield && !h->two_phase &&
-                      !fits_cache(h) && ceil_div(nx, 128) * ceil_div(h->p.ny, 4) >= 256;
+                      !fits_cache(h) && ceil_div(nx, 128) * ceil_div(h->p.ny, 4) >= h->cus;
   const bool one_only = (h->two_phase && variable_properties(h)) ||
                         (f64 && h->p.lattice != LBF_D3Q19 && !wide27);
   h->auto_slab = false;
@@ -539,7 +542,7 @@ Launch slab_launch(const lbfast_ctx* h) {
   // 5.7 us, 7.7 in the hardware's order; 32^3 4.1 and 3.8)
   l.xcd_remap = h->block_order != 0
                     ? h->block_order == 2
-                    : static_cast<int64_t>(l.tiles_x) * l.tiles_y * h->p.nz > 256;
+                    : static_cast<int64_t>(l.tiles_x) * l.tiles_y * h->p.nz > h->cus;
   return l;
 }
 
@@ -601,7 +604,7 @@ bool contiguous_order(const lbfast_ctx* h, int tiles_x, int tiles_y, bool adjoin
   if (fits_cache(h)) return cache_matters(h);
   if (h->two_phase && variable_properties(h)) return false;
   return h->p.storage == LBF_F64 && ((h->p.lattice == LBF_D3Q19 && !adjoint) ||
-                                     static_cast<int64_t>(tiles_x) * tiles_y > 256);
+                                     static_cast<int64_t>(tiles_x) * tiles_y > h->cus);
 }
 
 // The launches that the handle's settings come to; whatever changes one of them
@@ -615,9 +618,12 @@ void plan(lbfast_ctx* h) {
     h->step.cached = step_cached(h, sites, rows);
     h->step.xcd_remap = contiguous_order(h, h->step.tiles_x, h->step.tiles_y);
   }
-  if (h->two_phase)
-    h->phase = lbf::phase_geom(h->p.storage, static_cast<int>(h->p.nx),
-                               static_cast<int>(h->p.ny), static_cast<int>(h->p.nz));
+  if (h->two_phase) {
+    const int nx = static_cast<int>(h->p.nx), ny = static_cast<int>(h->p.ny);
+    const int nz = static_cast<int>(h->p.nz);
+    h->phase = lbf::phase_geom(h->p.storage, nx, ny, nz, h->cus);
+    h->force = lbf::force_geom(h->p.storage, h->pp.rho_l != h->pp.rho_h, nx, ny, nz, h->cus);
+  }
 }
 
 // problem and default launch shapes of a new handle
@@ -898,8 +904,14 @@ int lbfast_create(const lbfast_params* p, void* stream, void* buf0, void* buf1, 
 
   lbfast_ctx* h = new (std::nothrow) lbfast_ctx();
   if (!h) return fail(LBF_E_NOMEM, "host allocation failed");
-  set_params(h, p);
   h->device = dev;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+      cus > 0)
+    h->cus = cus;
+  else
+    (void)hipGetLastError();
+  set_params(h, p);
   h->stream = static_cast<hipStream_t>(stream);
   const size_t bytes = lbfast_buffer_bytes(p);
   for (int k = 0; k < 10; ++k) {
@@ -1275,8 +1287,8 @@ int lbfast_set_form(lbfast_t h, int form) {
   return LBF_OK;
 }
 
-int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_phase_params* pp,
-                          int what, lbfast_launch_info* out) {
+int lbfast_default_launch(const lbfast_params* p, int compute_units, int force_field,
+                          const lbfast_phase_params* pp, int what, lbfast_launch_info* out) {
   g_err.clear();
   if (int rc = validate(p)) return rc;
   if (!out) return fail(LBF_E_ARG, "out is NULL");
@@ -1286,7 +1298,9 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
                 sizeof(lbfast_phase_params));
   if (pp && p->storage == LBF_F16SU)
     return fail(LBF_E_UNSUPPORTED, "the two-component variant does not cover LBF_F16SU storage");
+  if (compute_units < 0) return fail(LBF_E_ARG, "compute_units must be >= 0");
   lbfast_ctx h;
+  if (compute_units) h.cus = compute_units;
   set_params(&h, p);
   if (force_field) {
     h.Ffield = out;  // any address: only whether there is one counts here
@@ -1308,11 +1322,7 @@ int lbfast_default_launch(const lbfast_params* p, int force_field, const lbfast_
   }
   if (what == LBF_LAUNCH_PHASE || what == LBF_LAUNCH_FORCE) {
     if (!pp) return fail(LBF_E_ARG, "a launch of the two-component variant");
-    const lbf::PassGeom g =
-        what == LBF_LAUNCH_PHASE
-            ? h.phase
-            : lbf::force_geom(p->storage, pp->rho_l != pp->rho_h, static_cast<int>(p->nx),
-                              static_cast<int>(p->ny), static_cast<int>(p->nz));
+    const lbf::PassGeom& g = what == LBF_LAUNCH_PHASE ? h.phase : h.force;
     out->lane_sites = 1;
     out->tile_rows = g.rows;
     out->z_chunk = g.zchunk;
@@ -1388,7 +1398,7 @@ int lbfast_enable_two_phase(lbfast_t h, const lbfast_phase_params* pp) {
   lbf::PhaseArgs pa = phase_args(h);
   pa.phi_out = h->phi[0];
   pa.F = h->Fph[0];
-  e = lbf::launch_capillary_force(h->p.storage, pa, h->stream);
+  e = lbf::launch_capillary_force(h->p.storage, pa, h->force, h->stream);
   if (e != hipSuccess) return hip_fail(e, "capillary force");
   return LBF_OK;
 }
@@ -1421,7 +1431,7 @@ int lbfast_set_phase(lbfast_t h, const void* phi, int dtype, int on_device) {
     lbf::PhaseArgs pa = phase_args(h);
     pa.phi_out = h->phi[h->pcur];
     pa.F = h->Fph[h->pcur];
-    e = lbf::launch_capillary_force(h->p.storage, pa, h->stream);
+    e = lbf::launch_capillary_force(h->p.storage, pa, h->force, h->stream);
   }
   if (staging) {
     hipError_t e2 = hipStreamSynchronize(h->stream);

@@ -493,11 +493,11 @@ __global__ void __launch_bounds__(64 * kUpdRows) grad_march_kernel(const C* __re
 // zc planes, run as zc + `extra` iterations (an even number).  An iteration
 // takes `lat` us where a CU has one workgroup and at least `busy` us for each
 // workgroup on it, so the cost of a launch is the product with the workgroups
-// on the fullest of the 256 CUs; the chunk length of the least cost, down to
+// on the fullest of the `cus` CUs; the chunk length of the least cost, down to
 // one plane on small grids.  Of equal costs (an odd length and the next even
 // one) the longer, but the shorter up to `shorter` workgroups.
 PassGeom march_geom(int nx, int ny, int nz, int rows, int extra, double lat, double busy,
-                    int64_t shorter = 0) {
+                    int cus, int64_t shorter = 0) {
   PassGeom m{};
   m.rows = rows;
   m.tiles_x = (nx + 63) / 64;
@@ -512,8 +512,8 @@ PassGeom march_geom(int nx, int ny, int nz, int rows, int extra, double lat, dou
     }
     last = zc;
     const int64_t blocks = cols * ((nz + zc - 1) / zc);
-    if (k > 1 && blocks > 4096) break;
-    const double per_cu = static_cast<double>((blocks + 255) / 256);
+    if (k > 1 && blocks > 16 * int64_t{cus}) break;
+    const double per_cu = static_cast<double>((blocks + cus - 1) / cus);
     const double cost = (zc + extra + 1) / 2 * 2 * (per_cu * busy > lat ? per_cu * busy : lat);
     if (k == 1 || cost < m.cost || (cost == m.cost && blocks <= shorter)) {
       m.cost = cost;
@@ -556,10 +556,10 @@ hipError_t phase_step_st(const PhaseArgs& a, const PassGeom& m, hipStream_t s) {
 // is best there, 4 / 16 rows: 32^3 16 / 21, 64^3 23.6 / 24.9, 128^3 92.8 /
 // 91.7, 256^3 518 / 514), and always 4 rows in FP64, where 16 spill (128^3
 // 160 / 185).
-PassGeom phase_geom(int storage, int nx, int ny, int nz) {
-  if (storage == kF64) return march_geom(nx, ny, nz, kLowRows, 5, 1.1, 0.9);
-  const PassGeom tall = march_geom(nx, ny, nz, kUpdRows, 5, 2.0, 2.0);
-  const PassGeom low = march_geom(nx, ny, nz, kLowRows, 5, 0.95, 0.55);
+PassGeom phase_geom(int storage, int nx, int ny, int nz, int cus) {
+  if (storage == kF64) return march_geom(nx, ny, nz, kLowRows, 5, 1.1, 0.9, cus);
+  const PassGeom tall = march_geom(nx, ny, nz, kUpdRows, 5, 2.0, 2.0, cus);
+  const PassGeom low = march_geom(nx, ny, nz, kLowRows, 5, 0.95, 0.55, cus);
   return low.cost < tall.cost ? low : tall;
 }
 
@@ -573,9 +573,9 @@ PassGeom phase_geom(int storage, int nx, int ny, int nz) {
 // shorter is the faster there (300 x 280 x 200 25 planes 218 us, 40 planes 230)
 // and as long as no CU has two workgroups (8 x 128 x 8 1 plane 7.2, 2 planes
 // 7.4), else the longer (77 x 150 x 210 FP32 27.4 and 28.9).  The choice takes 1.01 times as long as the best of the sweep.
-PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz) {
+PassGeom force_geom(int storage, bool contrast, int nx, int ny, int nz, int cus) {
   const double busy = !contrast ? (storage == kF64 ? 1.0 : 0.75) : (storage == kF32 ? 0.9 : 1.0);
-  return march_geom(nx, ny, nz, kUpdRows, 2, 1.0, busy, busy == 1.0 ? INT64_MAX : 256);
+  return march_geom(nx, ny, nz, kUpdRows, 2, 1.0, busy, cus, busy == 1.0 ? INT64_MAX : cus);
 }
 
 hipError_t launch_phase_step(int storage, const PhaseArgs& a, const PassGeom& m,
@@ -591,14 +591,13 @@ hipError_t launch_phase_step(int storage, const PhaseArgs& a, const PassGeom& m,
 
 namespace {
 template <int ST>
-hipError_t force_st(const PhaseArgs& a, hipStream_t s) {
+hipError_t force_st(const PhaseArgs& a, const PassGeom& m, hipStream_t s) {
   using C = typename Storage<ST>::C;
   using T = typename Storage<ST>::T;
   const C* phi = static_cast<const C*>(a.phi_out);
   const T* st = static_cast<const T*>(a.state);
   auto launch = [&](auto contrast) {
     using E = ForceEmit<ST, decltype(contrast)::value>;
-    const PassGeom m = force_geom(ST, decltype(contrast)::value, a.nx, a.ny, a.nz);
     hipLaunchKernelGGL((grad_march_kernel<C, E>), dim3(m.blocks), dim3(64 * kUpdRows), 0, s, phi, a.nx, a.ny, a.nz,
                        m.tiles_x, m.tiles_y, m.zchunk, a.walls_y != 0,
                        E{st, static_cast<C*>(a.F), a.N, a});
@@ -611,12 +610,13 @@ hipError_t force_st(const PhaseArgs& a, hipStream_t s) {
 }
 }  // namespace
 
-hipError_t launch_capillary_force(int storage, const PhaseArgs& a, hipStream_t s) {
+hipError_t launch_capillary_force(int storage, const PhaseArgs& a, const PassGeom& m,
+                                  hipStream_t s) {
   switch (storage) {
-    case kF64: return force_st<kF64>(a, s);
-    case kF32: return force_st<kF32>(a, s);
-    case kF16S: return force_st<kF16S>(a, s);
-    case kBF16S: return force_st<kBF16S>(a, s);
+    case kF64: return force_st<kF64>(a, m, s);
+    case kF32: return force_st<kF32>(a, m, s);
+    case kF16S: return force_st<kF16S>(a, m, s);
+    case kBF16S: return force_st<kBF16S>(a, m, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -41,13 +41,13 @@ def test_what_cannot_be_launched_is_refused():
 
     def rc(what, field=0, **kw):
         p = _lib.make_params((8, 8, 8), 0.8, **kw)
-        return lib.lbfast_default_launch(ctypes.byref(p), field, None, what, ctypes.byref(out))
+        return lib.lbfast_default_launch(ctypes.byref(p), 0, field, None, what, ctypes.byref(out))
 
     assert rc(_lib.LBF_LAUNCH_STEP) == _lib.LBF_OK
     assert rc(99) == _lib.LBF_E_ARG
     assert rc(_lib.LBF_LAUNCH_ADJOINT, storage="f16s") == _lib.LBF_E_UNSUPPORTED
     assert rc(_lib.LBF_LAUNCH_ADJOINT, lattice="27h") == _lib.LBF_E_UNSUPPORTED
-    assert lib.lbfast_default_launch(None, 0, None, 0, ctypes.byref(out)) == _lib.LBF_E_ARG
+    assert lib.lbfast_default_launch(None, 0, 0, None, 0, ctypes.byref(out)) == _lib.LBF_E_ARG
     assert lib.lbfast_set_form(None, 1) == _lib.LBF_E_ARG
 
 
@@ -122,3 +122,19 @@ def test_one_plane_form_against_its_memory_time(storage, Q, shape, kind, one_pla
     """The form that both forms' times name, by 15% or more: the one-plane form
     reads three planes for one, which decides on larger grids."""
     assert default_launch(shape, Q, storage, **kind)["one_plane"] == one_plane
+
+
+@pytest.mark.parametrize("what,phase", [(_lib.LBF_LAUNCH_STEP, None),
+                                        (_lib.LBF_LAUNCH_ADJOINT, None),
+                                        (_lib.LBF_LAUNCH_PHASE, EQUAL),
+                                        (_lib.LBF_LAUNCH_FORCE, EQUAL)])
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("shape", [(64, 64, 64), (128, 128, 128), (160, 150, 140)])
+def test_a_partition_with_fewer_compute_units(what, phase, storage, shape):
+    """A device partition of 32 compute units gets no more workgroups than the
+    whole device, and chunks at least as long."""
+    whole = default_launch(shape, 19, storage, phase=phase, what=what)
+    part = default_launch(shape, 19, storage, phase=phase, what=what, cus=32)
+    assert default_launch(shape, 19, storage, phase=phase, what=what, cus=256) == whole
+    assert part["blocks"] <= whole["blocks"] and part["z_chunk"] >= whole["z_chunk"]
+    assert part["blocks"] < whole["blocks"]
