@@ -227,7 +227,12 @@ bool variable_properties(const lbfast_ctx* h) {
 // both.  The others keep the parity of the planes that the chunks of
 // width_zchunk give, and where more than that matters these chunks themselves
 // and the rows of width_launch (BF16 D3Q19 48 x 104 x 46: 0.07% off after 29
-// steps in chunks of another even length).
+// steps in chunks of another even length).  FP16SU with D3Q19 and D3Q27 keeps
+// the parity alone, which its words need without a force; with a uniform force
+// low words of the velocity differ between tile heights (27 of 100 drawn grids
+// after 6 steps, at most 8e-4 of a state, 7e-8 of its largest value), which is
+// accepted: held to the 8 rows of width_launch, it took up to 1.6 times as long
+// (168 x 232 x 63 D3Q27 50.6 us, 82.0).
 bool keeps_parity(const lbfast_ctx* h) {
   return is_16bit(h->p.storage) &&
          (h->p.storage != LBF_F16S || h->p.lattice == LBF_D3Q27H || h->two_phase);
@@ -302,9 +307,11 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
 // the planes and their y and z halos, 128 bytes for every x-halo site and
 // stream, read at 9 TB/s, and the stores at 5.6 TB/s (plain ones, which stay
 // in the cache, are not counted); more than one workgroup per CU drift apart
-// and lose halo lines.  The shape it picks takes 1.03 times as long as the best
-// one of the sweep in the geometric mean (the rule before it, 64-plane chunks
-// and the tile height by storage form alone, 1.6 times).
+// and lose halo lines.  The shape it picks takes 1.04 times as long as the best
+// one of the sweep in the geometric mean over 461 grids and forms (64-plane
+// chunks and the tile height by storage form alone, 1.52 times).  Near ties go
+// wrong now and then: of 6000 drawn grids and forms 0.8% take 1.02 to 1.2 times as
+// long as with those, at a geometric mean of 0.52.
 double march_us(const MarchForm& f, int64_t nx, int64_t ny, int64_t nz, bool fits, bool cached,
                 int S, int ty, int64_t zc) {
   const double tx = static_cast<double>(ceil_div(nx, 64 * S));
@@ -357,7 +364,8 @@ int64_t best_zchunk(const lbfast_ctx* h, const MarchForm& f, int S, int ty, doub
   const bool fixed = keeps_rows(h) || (even_only && by_width % 2 != 0 && by_width < nz);
   // in contiguous order, chunks that come out whole on each of the 8 XCDs
   // share all their halo lines there (201 x 97 x 113 D3Q27 FP32 with a field: 8
-  // chunks 53 us, 9 chunks 60)
+  // chunks 53 us, 9 chunks 60; over 134 in-cache grids and forms of the sweep the
+  // choice is 0.4% faster for it, FP32 without a field 1.4%)
   const bool whole = !f.stencil && cache_matters(h);
   auto consider = [&](int64_t zc) {
     double t = march_us(f, nx, ny, nz, fits, cached, S, ty, zc);
@@ -480,7 +488,12 @@ void width_launch(lbfast_ctx* h) {
 //     against 199), for the two-component step with D3Q27 and D3Q27h with two
 //     sites or FP64 (256^3 FP32 645 us with two sites and 8 rows, 542 with one;
 //     192^3 FP64 938 us with 8 rows, 654 with 6), and for D3Q27h FP64 with a
-//     force field (8 spill: 130^3 181 us, 144 with 6).
+//     force field (8 spill: 130^3 181 us, 144 with 6).  With a uniform force
+//     instead, 8 rows spill 20 to 32 bytes and are as fast or faster (130^3 124
+//     and 137 us, 256^3 608 and 664, 192^3 302 and 281), and the two-site form of
+//     D3Q27, 44 to 80 bytes, is faster on some of the grids that take it and
+//     slower on others (384 x 384 x 256 1473 us, one site 1638; 512 x 512 x 300 2621
+//     and 2371).
 void model_launch(lbfast_ctx* h) {
   const int64_t nx = h->p.nx;
   const bool f64 = h->p.storage == LBF_F64;
@@ -591,7 +604,7 @@ int adjoint_rows(const lbfast_ctx* h, const MarchForm& f, int sites) {
 // D3Q27 and D3Q27h are as fast in either on 13 grids, but 320^3 1313 us against
 // 1115).  Elsewhere the hardware's order: marches of one wave of workgroups keep
 // step by themselves, and several waves lose about 10% in the other.  The
-// two-component step is no exception: on 50 grids and forms in the cache the
+// two-component step is no exception: on 52 grids and forms in the cache the
 // contiguous order takes 0.94 times as long in the geometric mean (180 x 90 x 60
 // FP32 51.8 us per step of both passes against 75, 201 x 97 x 113 125 against
 // 145; at most 1.2% slower), and for FP64 D3Q19 beyond it 0.97 (128^3 140 and 153,
