@@ -281,8 +281,8 @@ MarchForm march_form(const lbfast_ctx* h, bool adjoint = false) {
     f.slab += c64 ? 2.0 : 1.0;
   f.slab_mem = c * ((f.stencil ? 70 : h->Ffield ? 50 : 30) + (full ? 20 : 0));
   if (adjoint) f.slab = c64 ? 12.0 : 10.0, f.slab_mem = 80 * c;
-  // fitted to the times of 250 to 900 launch shapes on each of 67 grids (8 x
-  // 29 x 168 to 512^3), per velocity set and compute type
+  // fitted to the times of 50 to 900 launch shapes per grid (9 x 16 x 17 to
+  // 512^3), per velocity set and compute type
   const bool f64 = f.storage == LBF_F64;
   if (f.Q == LBF_D3Q19) {
     f.l0 = 0.45, f.l1 = f64 ? 0.15 : 0.07, f.busy = f64 ? 0.19 : 0.09;
